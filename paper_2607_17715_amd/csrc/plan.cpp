@@ -6,7 +6,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <limits>
+#include <queue>
 #include <sstream>
 
 #include "plan.hpp"
@@ -33,6 +35,44 @@ std::vector<double> rope_theta(int D, double base) {
   for (int i = 0; i < D / 2; ++i) th[i] = std::pow(base, -2.0 * i / D);
   return th;
 }
+
+constexpr int kXcds = 8;
+
+// Costs in key tiles of a 256-row block, for choosing between work lists: what an
+// item costs beside its tiles, the launch of the merge, and the bytes of partials
+// that take as long as a tile.
+constexpr int64_t kItemTiles = 3;
+constexpr double kMergeTiles = 2.0;
+constexpr double kTileBytes = 4e6;
+constexpr int32_t kMinPiece = 2;      // shortest piece of a row block cut by slot
+// A cut by slot is taken from this share of the even splits' time down; above it the
+// model's error decides (256 ragged row blocks, one per CU: splitting 8 to 72 of them
+// left the attention at 107-108 us and added a merge of 4-7 us).
+constexpr double kCutGain = 0.95;
+
+// A work list: items, by the XCD that runs them, and the row blocks to merge.
+struct Work {
+  std::vector<WorkItem> items;
+  std::vector<std::vector<WorkItem>> queue{kXcds};
+  std::vector<MergeGroup> merges;
+  int32_t n_partials = 0, max_splits = 1;
+
+  // merge group of a row block with `ns` splits (-1 where it has one)
+  int32_t add_merge(int32_t b, int32_t g, int32_t row0, int32_t nrows, int32_t ns) {
+    max_splits = std::max(max_splits, ns);
+    if (ns == 1) return -1;
+    merges.push_back({b, g, row0, nrows, n_partials, ns, 0, 0});
+    n_partials += ns;
+    return static_cast<int32_t>(merges.size()) - 1;
+  }
+  // heaviest items first
+  void sort_queues() {
+    for (auto& q : queue)
+      std::stable_sort(q.begin(), q.end(), [](const WorkItem& a, const WorkItem& b) {
+        return (a.tile1 - a.tile0) > (b.tile1 - b.tile0);
+      });
+  }
+};
 
 }  // namespace
 
@@ -315,25 +355,61 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
         groups.push_back(std::move(gr));
       }
   }
+  // ---- workspace layout of a work list --------------------------------------------
+  const int D = cfg.head_dim, H = D / 2;
+  const int64_t total = static_cast<int64_t>(p.slot_src.size());
+  // one cos/sin row per segment (angle delta * theta_i), or per slot for keys
+  // stored before RoPE (angle p_new * theta_i); slot_info's second field is the row
+  const int64_t cs_rows = p.keys_pre_rope ? total : nseg;
+  auto layout = [&](const Work& wk) {
+    WorkspaceLayout w;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = off;
+      off = align256(off + std::max<size_t>(bytes, 4));
+      return at;
+    };
+    w.req_slot0 = take(sizeof(int32_t) * (B + 1));
+    w.slot_info = take(sizeof(int32_t) * 2 * total);
+    w.slot_pos = take(sizeof(int32_t) * total);
+    w.seg_cs = take(sizeof(float) * 2 * size_t(std::max<int64_t>(cs_rows, 1)) * H);
+    w.suf_cs = take(sizeof(float) * 2 * size_t(B) * S * H);
+    w.block_table = take(sizeof(int32_t) * p.block_table.size());
+    w.compose_tiles = take(sizeof(int32_t) * p.compose_tiles.size());
+    w.items = take(sizeof(WorkItem) * wk.items.size());
+    w.merges = take(sizeof(MergeGroup) * wk.merges.size());
+    w.counters = take(sizeof(int32_t) * wk.merges.size());
+    w.table_bytes = off;
+    const size_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
+    w.part_o = take(act_bytes * size_t(wk.n_partials) * RB * D);
+    w.part_lse = take(sizeof(float) * size_t(wk.n_partials) * RB);
+    w.total = off;
+    return w;
+  };
+
   // Key splits only add parallelism where the row blocks alone leave CUs idle;
   // with at least one row block per CU they would only add partials, a merge
   // and a second round of workgroups.
   const bool split = int64_t(groups.size()) < target;
   const int64_t per_item =
       split ? std::max<int64_t>(1, (total_tiles + target - 1) / target) : INT32_MAX;
-  std::vector<WorkItem> items;
+  auto item_of = [&](const Group& gr, int32_t t0, int32_t t1, int32_t partial, int32_t merge) {
+    return WorkItem{gr.b, gr.g, gr.row0, gr.nrows, t0, t1, partial, merge,
+                    p.req_slot0[gr.b], p.req_slot0[gr.b + 1] - p.req_slot0[gr.b],
+                    p.block_table[size_t(gr.b) * p.max_pages], 0, {0, 0, 0}, 0};
+  };
+  Work even_splits;
   for (const Group& gr : groups) {
+    Work& wk = even_splits;
     // a SIF row block over several key ranges is one item that runs through
     // them in turn (no partials, no merge), when its tiles fit 16-bit fields
     if (sif && gr.ranges.size() > 1 && gr.ranges.size() <= 3 &&
         gr.ranges.back().second < 65536 && o.kv_splits == 0) {
-      WorkItem w{gr.b, gr.g, gr.row0, gr.nrows, 0, gr.tiles, -1, -1,
-                 p.req_slot0[gr.b], p.req_slot0[gr.b + 1] - p.req_slot0[gr.b],
-                 p.block_table[size_t(gr.b) * p.max_pages], int32_t(gr.ranges.size()),
-                 {0, 0, 0}, 0};
+      WorkItem w = item_of(gr, 0, gr.tiles, -1, -1);
+      w.n_ranges = int32_t(gr.ranges.size());
       for (size_t ri = 0; ri < gr.ranges.size(); ++ri)
         w.rng[ri] = gr.ranges[ri].first | (gr.ranges[ri].second << 16);
-      items.push_back(w);
+      wk.items.push_back(w);
       continue;
     }
     // splits of each range, at most kMaxSplits in all
@@ -356,44 +432,27 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
       nsr.push_back(k);
       ns += k;
     }
-    p.max_splits = std::max(p.max_splits, ns);
-    int32_t part0 = -1, merge = -1;
-    if (ns > 1) {
-      part0 = p.n_partials;
-      merge = static_cast<int32_t>(p.merges.size());
-      p.merges.push_back({gr.b, gr.g, gr.row0, gr.nrows, part0, ns, 0, 0});
-      p.n_partials += ns;
-    }
-    int32_t k = 0;
+    const int32_t merge = wk.add_merge(gr.b, gr.g, gr.row0, gr.nrows, ns);
+    int32_t part = merge < 0 ? -1 : wk.merges.back().part0;
     for (size_t ri = 0; ri < gr.ranges.size(); ++ri) {
       const int32_t first = gr.ranges[ri].first, len = gr.ranges[ri].second - first;
-      for (int s = 0; s < nsr[ri]; ++s, ++k) {
+      for (int s = 0; s < nsr[ri]; ++s) {
         const int32_t t0 = first + static_cast<int32_t>(int64_t(len) * s / nsr[ri]);
         const int32_t t1 = first + static_cast<int32_t>(int64_t(len) * (s + 1) / nsr[ri]);
-        items.push_back({gr.b, gr.g, gr.row0, gr.nrows, t0, t1, ns > 1 ? part0 + k : -1, merge,
-                         p.req_slot0[gr.b], p.req_slot0[gr.b + 1] - p.req_slot0[gr.b],
-                         p.block_table[size_t(gr.b) * p.max_pages], 0, {0, 0, 0}, 0});
+        wk.items.push_back(item_of(gr, t0, t1, merge < 0 ? -1 : part++, merge));
       }
     }
   }
-  // never chosen automatically: each split's agent-scope release writes back its
-  // XCD's whole L2 and the last split's acquire invalidates it, which costs the
-  // other workgroups there their cached keys and values (measured 2-5x slower
-  // than the separate merge kernel)
-  p.merge_in_kernel = o.merge_mode == 1;
-
   // XCD-aware order.  Workgroups are dealt to the 8 XCDs round-robin by index,
   // and each XCD has its own L2.  Items of one (request, kv-head) read the same
   // keys, values and queries, so they are kept on one XCD: (b, g) pairs go to the
-  // least-loaded XCD queue, queues hold their heaviest items first, and the
-  // grid interleaves the queues.
-  constexpr int kXcds = 8;
-  std::vector<std::vector<WorkItem>> queue(kXcds);
-  std::vector<int64_t> load(kXcds, 0);
+  // least-loaded XCD queue.
   {
+    std::vector<int64_t> load(kXcds, 0);
     std::vector<std::pair<int64_t, int64_t>> pairs;   // (-tiles, b * H + g)
     std::vector<int64_t> tiles_of(size_t(B) * cfg.n_kv_heads, 0);
-    for (const WorkItem& w : items) tiles_of[size_t(w.b) * cfg.n_kv_heads + w.g] += w.tile1 - w.tile0;
+    for (const WorkItem& w : even_splits.items)
+      tiles_of[size_t(w.b) * cfg.n_kv_heads + w.g] += w.tile1 - w.tile0;
     for (size_t k = 0; k < tiles_of.size(); ++k) pairs.push_back({-tiles_of[k], int64_t(k)});
     std::sort(pairs.begin(), pairs.end());
     std::vector<int> bin_of(tiles_of.size(), 0);
@@ -402,47 +461,124 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
       bin_of[pr.second] = x;
       load[x] += -pr.first;
     }
-    for (const WorkItem& w : items) queue[bin_of[size_t(w.b) * cfg.n_kv_heads + w.g]].push_back(w);
-    for (auto& q : queue)
-      std::stable_sort(q.begin(), q.end(), [](const WorkItem& a, const WorkItem& b) {
-        return (a.tile1 - a.tile0) > (b.tile1 - b.tile0);
-      });
-  }
-  std::vector<size_t> head(kXcds, 0);
-  for (size_t n = 0; n < items.size(); ++n) {
-    int x = static_cast<int>(n % kXcds);
-    if (head[x] >= queue[x].size()) {           // this queue ran dry: take the fullest one
-      size_t best = 0;
-      for (int y = 0; y < kXcds; ++y)
-        if (queue[y].size() - head[y] > best) { best = queue[y].size() - head[y]; x = y; }
-    }
-    p.items.push_back(queue[x][head[x]++]);
+    for (const WorkItem& w : even_splits.items)
+      even_splits.queue[bin_of[size_t(w.b) * cfg.n_kv_heads + w.g]].push_back(w);
   }
 
+  // The same row blocks cut where a workgroup slot is full: the slots are filled
+  // one after the other to the least load (tiles and cost per item) at which they
+  // hold all tiles, so that every slot has the same load whatever the number of
+  // row blocks.  A row block has as many splits as the slots it lies over, of
+  // unequal length; the short pieces pair up with others in the dispatch order
+  // (longest first).  Consecutive slots belong to one XCD, so a (request,
+  // kv-head) still stays on one or two of them.  Measured: 144 row blocks of 77
+  // tiles on 256 CUs, which two equal splits each took in a full round and a
+  // nearly empty one, 182 -> 135 us; 192 decode row blocks of 59 tiles in three
+  // splits on 512 slots, 86.5 -> 73.6 us.
+  struct Piece { int32_t end; int64_t slot; };       // of a row block, from the last one's end
+  std::vector<std::vector<Piece>> pieces;
+  auto fill_slots = [&](int64_t load) {              // the number of slots taken
+    pieces.assign(groups.size(), {});
+    int64_t slot = 0, room = load;
+    for (size_t i = 0; i < groups.size(); ++i)
+      for (int32_t t = 0; t < groups[i].tiles;) {
+        const int32_t left = groups[i].tiles - t;
+        int64_t n = std::min<int64_t>(left, room - kItemTiles);
+        if (n < left && left - n < kMinPiece) n = left - kMinPiece;
+        if (int32_t(pieces[i].size()) == kMaxSplits - 1) n = left;
+        if (n < std::min(left, kMinPiece)) {
+          ++slot;
+          room = load;
+          continue;
+        }
+        t += static_cast<int32_t>(n);
+        room -= n + kItemTiles;
+        pieces[i].push_back({t, slot});
+      }
+    return slot + 1;
+  };
+  auto cut_by_slot = [&]() {
+    Work wk;
+    int64_t lo = kItemTiles + 2 * kMinPiece;
+    int64_t hi = std::max(lo, total_tiles + kItemTiles * int64_t(groups.size()));
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (fill_slots(mid) <= target) hi = mid;
+      else lo = mid + 1;
+    }
+    const int64_t n_slots = fill_slots(lo);
+    for (size_t i = 0; i < groups.size(); ++i) {
+      const Group& gr = groups[i];
+      const int32_t merge = wk.add_merge(gr.b, gr.g, gr.row0, gr.nrows, int32_t(pieces[i].size()));
+      int32_t part = merge < 0 ? -1 : wk.merges.back().part0, t = 0;
+      for (const Piece& pc : pieces[i]) {
+        const WorkItem w = item_of(gr, t, pc.end, merge < 0 ? -1 : part++, merge);
+        wk.items.push_back(w);
+        wk.queue[pc.slot * kXcds / n_slots].push_back(w);
+        t = pc.end;
+      }
+    }
+    return wk;
+  };
+  // Time of a work list in key tiles: the busiest XCD's slots, filled longest item
+  // first, and the merge (its launch, and its partials written and read).
+  auto makespan = [&](Work& wk) {
+    const int64_t slots = std::max<int64_t>(1, target / kXcds);
+    double worst = 0;
+    for (auto& q : wk.queue) {
+      std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
+      int64_t last = 0;
+      for (const WorkItem& w : q) {
+        int64_t at = 0;
+        if (int64_t(free_at.size()) == slots) { at = free_at.top(); free_at.pop(); }
+        at += w.tile1 - w.tile0 + kItemTiles;
+        last = std::max(last, at);
+        free_at.push(at);
+      }
+      worst = std::max(worst, double(last));
+    }
+    if (!wk.merges.empty())
+      worst += kMergeTiles;
+    for (const MergeGroup& m : wk.merges)
+      worst += double(m.nsplit) * m.nrows * cfg.head_dim *
+               (cfg.act_dtype == C2KV_F32 ? 4 : 2) / kTileBytes;
+    return worst;
+  };
+  even_splits.sort_queues();
+  Work* work = &even_splits;
+  Work by_slot;
+  if (!sif && o.kv_splits == 0) {
+    by_slot = cut_by_slot();
+    by_slot.sort_queues();
+    if (makespan(by_slot) < kCutGain * makespan(even_splits) &&
+        (layout(by_slot).total <= C2KV_STATIC_SCRATCH_BYTES ||
+         layout(even_splits).total > C2KV_STATIC_SCRATCH_BYTES))
+      work = &by_slot;
+  }
+  // never chosen automatically: each split's agent-scope release writes back its
+  // XCD's whole L2 and the last split's acquire invalidates it, which costs the
+  // other workgroups there their cached keys and values (measured 2-5x slower
+  // than the separate merge kernel)
+  p.merge_in_kernel = o.merge_mode == 1;
+
+  // the grid interleaves the XCDs' queues
+  std::vector<size_t> head(kXcds, 0);
+  for (size_t n = 0; n < work->items.size(); ++n) {
+    int x = static_cast<int>(n % kXcds);
+    if (head[x] >= work->queue[x].size()) {     // this queue ran dry: take the fullest one
+      size_t best = 0;
+      for (int y = 0; y < kXcds; ++y)
+        if (work->queue[y].size() - head[y] > best) { best = work->queue[y].size() - head[y]; x = y; }
+    }
+    p.items.push_back(work->queue[x][head[x]++]);
+  }
+  p.ws = layout(*work);
+  p.merges = std::move(work->merges);
+  p.n_partials = work->n_partials;
+  p.max_splits = work->max_splits;
+
   // ---- workspace image --------------------------------------------------------
-  const int D = cfg.head_dim, H = D / 2;
-  const int64_t total = static_cast<int64_t>(p.slot_src.size());
-  WorkspaceLayout& w = p.ws;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t at = off; off = align256(off + std::max<size_t>(bytes, 4)); return at; };
-  w.req_slot0 = take(sizeof(int32_t) * (B + 1));
-  w.slot_info = take(sizeof(int32_t) * 2 * total);
-  w.slot_pos = take(sizeof(int32_t) * total);
-  // one cos/sin row per segment (angle delta * theta_i), or per slot for keys
-  // stored before RoPE (angle p_new * theta_i); slot_info's second field is the row
-  const int64_t cs_rows = p.keys_pre_rope ? total : nseg;
-  w.seg_cs = take(sizeof(float) * 2 * size_t(std::max<int64_t>(cs_rows, 1)) * H);
-  w.suf_cs = take(sizeof(float) * 2 * size_t(B) * S * H);
-  w.block_table = take(sizeof(int32_t) * p.block_table.size());
-  w.compose_tiles = take(sizeof(int32_t) * p.compose_tiles.size());
-  w.items = take(sizeof(WorkItem) * p.items.size());
-  w.merges = take(sizeof(MergeGroup) * p.merges.size());
-  w.counters = take(sizeof(int32_t) * p.merges.size());
-  w.table_bytes = off;
-  const size_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
-  w.part_o = take(act_bytes * size_t(p.n_partials) * RB * D);
-  w.part_lse = take(sizeof(float) * size_t(p.n_partials) * RB);
-  w.total = off;
+  const WorkspaceLayout& w = p.ws;
 
   p.image.assign(w.table_bytes, 0);
   auto put = [&](size_t at, const void* src, size_t bytes) {

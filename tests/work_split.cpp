@@ -1,0 +1,84 @@
+// Checks the attention work list of ragged batches (plan.cpp, host code only):
+// the items of every row block cover its key tiles exactly once, in order, each
+// split with a partial of its own inside its merge group.
+// Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n>" (cut: plans with
+// row blocks split in unequal numbers of pieces, though no count was asked for).
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <set>
+#include <tuple>
+#include <vector>
+#include "plan.hpp"
+using namespace c2kv;
+#define CHECK(c) do { if (!(c)) { std::printf("FAIL %s line %d iter %d\n", #c, __LINE__, it); return 1; } } while (0)
+int main(int argc, char** argv) {
+  const int iters = argc > 1 ? atoi(argv[1]) : 300;
+  std::mt19937_64 rng(argc > 2 ? atoll(argv[2]) : 1);
+  auto U = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
+  int cut = 0;
+  for (int it = 0; it < iters; ++it) {
+    c2kv_attn_cfg cfg{};
+    const int hk[] = {1, 2, 4, 8}, G[] = {1, 3, 4, 8};
+    cfg.n_kv_heads = hk[U(0, 3)];
+    cfg.n_q_heads = cfg.n_kv_heads * G[U(0, 3)];
+    cfg.head_dim = U(0, 1) ? 64 : 128;
+    cfg.act_dtype = U(0, 3) == 0 ? C2KV_F32 : C2KV_BF16;
+    cfg.rope_base = 1e4;
+    c2kv_plan_opts o{};
+    const int cus[] = {0, 8, 20, 256};
+    o.num_cus = cus[U(0, 3)];
+    const int B = U(1, 12), S = U(0, 1) ? U(1, 4) : U(5, 300), most = U(0, 3) ? U(1, 6000) : 0;
+    std::vector<int32_t> req_off(B + 1, 0), span, orig, koff{0}, kept;
+    std::vector<int64_t> row0;
+    for (int b = 0; b < B; ++b) {
+      const int n = most ? U(most / 3, most) : 0;
+      if (n > 0) {
+        row0.push_back(0);
+        span.push_back(n);
+        orig.push_back(0);
+        for (int i = 0; i < n; ++i) kept.push_back(i);
+        koff.push_back(int32_t(kept.size()));
+      }
+      req_off[b + 1] = int32_t(span.size());
+    }
+    c2kv_compose_desc d{};
+    d.batch = B; d.n_segments = int32_t(span.size()); d.req_seg_off = req_off.data();
+    d.seg_row0 = row0.data(); d.seg_span = span.data(); d.seg_orig_pos0 = orig.data();
+    d.seg_kept_off = koff.data(); d.kept_idx = kept.data();
+    Plan p;
+    std::string err;
+    CHECK(build_plan(cfg, d, S, &o, p, err) == C2KV_OK);
+
+    const int g = cfg.n_q_heads / cfg.n_kv_heads, R = g * S, RB = p.rows_per_block;
+    std::map<std::tuple<int, int, int>, std::vector<WorkItem>> blocks;
+    for (const auto& w : p.items) blocks[{w.b, w.g, w.row0}].push_back(w);
+    CHECK(int64_t(blocks.size()) == int64_t(B) * cfg.n_kv_heads * ((R + RB - 1) / RB));
+    std::set<int> partials, sizes;
+    for (auto& kv : blocks) {
+      auto& v = kv.second;
+      std::sort(v.begin(), v.end(), [](const WorkItem& x, const WorkItem& y) { return x.tile0 < y.tile0; });
+      const int n = p.req_slot0[v[0].b + 1] - p.req_slot0[v[0].b];
+      const int rows = std::min(RB, R - v[0].row0), tmax = (v[0].row0 + rows - 1) / g;
+      CHECK(v.front().tile0 == 0 && v.back().tile1 == (n + 63) / 64 + (tmax + 64) / 64);
+      sizes.insert(int(v.size()));
+      for (size_t i = 0; i < v.size(); ++i) {
+        CHECK(v[i].nrows == rows && v[i].tile0 < v[i].tile1);
+        if (i) CHECK(v[i].tile0 == v[i - 1].tile1);
+        if (v.size() == 1) { CHECK(v[i].partial == -1 && v[i].merge == -1); continue; }
+        CHECK(v[i].merge >= 0 && v[i].merge < int(p.merges.size()));
+        const MergeGroup& m = p.merges[v[i].merge];
+        CHECK(m.b == v[i].b && m.g == v[i].g && m.row0 == v[i].row0 && m.nrows == rows);
+        CHECK(m.nsplit == int(v.size()) && m.nsplit <= p.max_splits && m.nsplit <= kMaxSplits);
+        CHECK(v[i].partial == m.part0 + int(i) && partials.insert(v[i].partial).second);
+      }
+    }
+    CHECK(int(partials.size()) == p.n_partials);
+    CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * RB <= p.ws.total);
+    if (sizes.size() > 1 && *sizes.rbegin() <= 8) ++cut;
+  }
+  std::printf("ok %d cut %d\n", iters, cut);
+  return 0;
+}
