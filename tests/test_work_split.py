@@ -8,6 +8,7 @@ import shutil
 import subprocess
 
 import pytest
+import torch  # noqa: F401  (before the library, so that both share one HIP runtime)
 
 import paper_2607_17715_amd as c2kv
 import synth
