@@ -247,7 +247,7 @@ struct AttnParams {
   const int* block_table;
   const WorkItem* items;
   const MergeGroup* merges;
-  int* counters;                // [n_merge], zero between launches
+  unsigned* counters;           // [n_merge], zero between launches
   const void* k;                // pages or pool
   const void* v;
   const float* k_scale;
@@ -354,54 +354,151 @@ struct RowKeys {
 };
 
 // ----------------------------------------------------------------------------
-// log-sum-exp combine of the key splits of one row block (rows [rlo, rhi))
+// log-sum-exp combine of the key splits of one row block, by the workgroup whose
+// split finished last
 // ----------------------------------------------------------------------------
 
-template <typename T, int D>
-__device__ inline void merge_rows(const MergeGroup& mg, int rlo, int rhi, const void* part_o,
-                                  const float* part_lse, int RB, int Hq, int G, int S,
-                                  void* out, float* lse, int tid, int nthr) {
-  constexpr int TPR = D / 4;
-  for (int idx = tid; idx < (rhi - rlo) * TPR; idx += nthr) {
-    const int rloc = rlo + idx / TPR;
-    const int d = 4 * (idx % TPR);
-    const float* pl = part_lse + size_t(mg.part0) * RB + rloc;
-    const T* po = static_cast<const T*>(part_o) + (size_t(mg.part0) * RB + rloc) * D + d;
-    float mx = kNegInf;
-#pragma unroll 8
-    for (int i = 0; i < mg.nsplit; ++i) mx = fmaxf(mx, pl[size_t(i) * RB]);
-    float z = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int i = 0; i < mg.nsplit; ++i) {
-      const float li = pl[size_t(i) * RB];
-      const float w = (li == kNegInf) ? 0.f : __expf(li - mx);
-      float4 v;
-      if constexpr (sizeof(T) == 4) {
-        v = *reinterpret_cast<const float4*>(po + size_t(i) * RB * D);
-      } else {
-        const uint2 u = *reinterpret_cast<const uint2*>(po + size_t(i) * RB * D);
-        v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-      }
-      z += w;
-      acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
-    }
+// Partials that another workgroup of the same launch reads are stored and loaded at
+// agent scope, access by access (sc1: written through and read past the L2s of the
+// XCDs, which are not coherent with each other), so that no workgroup writes back or
+// invalidates a whole L2 under the others' cached keys and values, as agent-scope
+// fences do (decode at 16k/8x with them: 21.5 us a step, so 12.1 us; the separate
+// merge kernel 11.6 us; at system scope, sc0 sc1, 12.9 us).
+constexpr int kAgentScope = 16;
+
+__device__ inline float load_shared(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Each thread takes 16-byte chunks of the rows.  With chunks for all threads, UB of
+// them at a time over batches of NB splits; with fewer (decode), the splits are also
+// spread over `lanes` sets of threads, combined through LDS (`xs`).  Bound by the
+// latency of the loads, which are all in flight within a batch.
+template <typename T, int D, int NT>
+__device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnParams& a, float* xs,
+                                             int tid) {
+  constexpr int EPT = 16 / int(sizeof(T));      // elements per chunk
+  constexpr int CPR = D / EPT;                  // chunks per row
+  const int units = mg.nrows * CPR, ns = mg.nsplit;
+  const float* pl = a.part_lse + size_t(mg.part0) * a.RB;
+  const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(
+      static_cast<T*>(a.part_o) + size_t(mg.part0) * a.RB * D, 0,
+      ns * a.RB * D * int(sizeof(T)), kBufferFlags);
+  auto store_row = [&](int u, float mx, float z, const float (&acc)[EPT])
+      __attribute__((always_inline)) {
+    const int rloc = u / CPR, e0 = (u % CPR) * EPT;
     const float inv = z > 0.f ? 1.f / z : 0.f;
     const int r = mg.row0 + rloc;
-    const int t = r / G, h = mg.g * G + r % G;
-    T* orow = static_cast<T*>(out) + ((size_t(mg.b) * S + t) * Hq + h) * D;
+    const int t = r / a.G, h = mg.g * a.G + r % a.G;
+    T* dst = static_cast<T*>(a.out) + ((size_t(mg.b) * a.S + t) * a.Hq + h) * D + e0;
     if constexpr (sizeof(T) == 4) {
-      *reinterpret_cast<float4*>(orow + d) =
-          make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+      *reinterpret_cast<float4*>(dst) =
+          make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
     } else {
-      uint2 u;
-      u.x = pack_bf16(acc.x * inv, acc.y * inv);
-      u.y = pack_bf16(acc.z * inv, acc.w * inv);
-      *reinterpret_cast<uint2*>(orow + d) = u;
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = acc[e] * inv;
+      store8(reinterpret_cast<__bf16*>(dst), x);
     }
-    if (lse && d == 0) lse[(size_t(mg.b) * Hq + h) * S + t] = z > 0.f ? mx + __logf(z) : kNegInf;
+    if (a.lse && e0 == 0)
+      a.lse[(size_t(mg.b) * a.Hq + h) * a.S + t] = z > 0.f ? mx + __logf(z) : kNegInf;
+  };
+  // chunks u0 + k * ustep (k < UB, those below `units`), splits i0, i0 + istep, ...
+  auto combine = [&](auto ub_c, auto nb_c, int u0, int ustep, int i0, int istep, float* mx,
+                     float* z, float (*acc)[EPT]) __attribute__((always_inline)) {
+    constexpr int UB = decltype(ub_c)::value, NB = decltype(nb_c)::value;
+#pragma unroll
+    for (int k = 0; k < UB; ++k) {
+      mx[k] = kNegInf;
+      z[k] = 0.f;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) acc[k][e] = 0.f;
+    }
+    for (int i = i0; i < ns; i += NB * istep) {
+      float l[UB][NB];
+      uint32_t w[UB][NB][4];
+      // unconditional loads from clamped indices; splits past the last get weight 0
+#pragma unroll
+      for (int k = 0; k < UB; ++k) {
+        const int u = min(u0 + k * ustep, units - 1);
+        const int rloc = u / CPR;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const int sp = min(i + j * istep, ns - 1);
+          l[k][j] = load_shared(pl + size_t(sp) * a.RB + rloc);
+          const auto x = __builtin_amdgcn_raw_buffer_load_b128(
+              po, ((sp * a.RB + rloc) * D + (u % CPR) * EPT) * int(sizeof(T)), 0, kAgentScope);
+          w[k][j][0] = x[0]; w[k][j][1] = x[1]; w[k][j][2] = x[2]; w[k][j][3] = x[3];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < UB; ++k) {
+        float m = mx[k];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          if (i + j * istep >= ns) l[k][j] = kNegInf;
+          m = fmaxf(m, l[k][j]);
+        }
+        const float mr = m == kNegInf ? 0.f : m;
+        const float old = __expf(mx[k] - mr);
+        z[k] *= old;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) acc[k][e] *= old;
+        mx[k] = m;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const float wt = __expf(l[k][j] - mr);
+          z[k] += wt;
+          if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[k][e] += wt * __uint_as_float(w[k][j][e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              acc[k][2 * e] += wt * __uint_as_float(w[k][j][e] << 16);
+              acc[k][2 * e + 1] += wt * __uint_as_float(w[k][j][e] & 0xffff0000u);
+            }
+          }
+        }
+      }
+    }
+  };
+  if (2 * units > NT) {
+    constexpr int UB = 4;
+    float mx[UB], z[UB], acc[UB][EPT];
+    for (int u0 = tid; u0 < units; u0 += UB * NT) {
+      combine(std::integral_constant<int, UB>{}, std::integral_constant<int, 4>{}, u0, NT, 0, 1,
+              mx, z, acc);
+#pragma unroll
+      for (int k = 0; k < UB; ++k)
+        if (u0 + k * NT < units) store_row(u0 + k * NT, mx[k], z[k], acc[k]);
+    }
+    return;
   }
+  const int lanes = min(NT / units, ns);        // >= 1
+  const int sl = tid / units, u = tid % units;
+  float mx[1], z[1], acc[1][EPT];
+  float* mine = xs + size_t(tid) * (EPT + 2);
+  if (sl < lanes) {
+    combine(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, u, 0, sl, lanes,
+            mx, z, acc);
+    mine[0] = mx[0];
+    mine[1] = z[0];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) mine[2 + e] = acc[0][e];
+  }
+  __syncthreads();
+  if (sl != 0) return;
+  for (int j = 1; j < lanes; ++j) {
+    const float* x = mine + size_t(j) * units * (EPT + 2);
+    const float m = fmaxf(mx[0], x[0]), mr = m == kNegInf ? 0.f : m;
+    const float w0 = __expf(mx[0] - mr), w1 = __expf(x[0] - mr);
+    mx[0] = m;
+    z[0] = z[0] * w0 + x[1] * w1;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) acc[0][e] = acc[0][e] * w0 + x[2 + e] * w1;
+  }
+  store_row(u, mx[0], z[0], acc[0]);
 }
 
 // ----------------------------------------------------------------------------
@@ -740,8 +837,10 @@ struct TileLoader {
 // groups of 32 rows (128 rows per 512 threads, 64 per 256) each see one half of
 // every 64-key tile, keep their own online softmax, and the two halves are
 // combined through LDS at the end.  256-thread workgroups (64-row blocks) run two
-// to a CU, so that two work items' latencies overlap.
-template <typename T, int D, int SRC, int KG, int NT>
+// to a CU, so that two work items' latencies overlap.  MERGE: the last split of a row
+// block merges it where the plan says so (kernels of their own: the merge raises the
+// registers of some, and SIF extraction measured 1.1 % slower with it behind a branch).
+template <typename T, int D, int SRC, int KG, int NT, bool MERGE>
 __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   constexpr int NRG = NT / 64 / KG;         // row groups
   constexpr int NKB = 2 / KG;               // 32-key blocks per wavefront and tile
@@ -764,7 +863,7 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   // two stages of [keys | transposed values]
   constexpr int SBUF = 2 * L::TILE;
   __shared__ __attribute__((aligned(16))) T sbuf[SBUF];
-  __shared__ int s_last;
+  __shared__ int s_last;      // (MERGE)
   auto kst = [&](int i) { return sbuf + i * L::TILE; };
   auto vst = [&](int i) { return sbuf + i * L::TILE + KT * L::LDK; };
 
@@ -1293,7 +1392,11 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       if (it.partial < 0) {
         if (a.lse) a.lse[(size_t(b) * a.Hq + h) * S + t] = lse_val;
       } else {
-        a.part_lse[size_t(it.partial) * a.RB + rloc] = lse_val;
+        float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
+        if constexpr (MERGE)
+          __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          *dst = lse_val;
       }
     }
   }
@@ -1307,40 +1410,36 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       const T* src = sbuf + rl * LDO + e0;
       const uint2 lo = *reinterpret_cast<const uint2*>(src);
       const uint2 hi = *reinterpret_cast<const uint2*>(src + EPC / 2);
-      T* dst;
       if (it.partial < 0) {
         const int r = it.row0 + rl;
-        dst = static_cast<T*>(a.out) + ((size_t(b) * S + r / G) * a.Hq + g * G + r % G) * D + e0;
+        T* dst = static_cast<T*>(a.out) + ((size_t(b) * S + r / G) * a.Hq + g * G + r % G) * D + e0;
+        *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
       } else {
-        dst = static_cast<T*>(a.part_o) + (size_t(it.partial) * a.RB + rl) * D + e0;
+        const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
+            static_cast<T*>(a.part_o) + size_t(it.partial) * a.RB * D, 0,
+            a.RB * D * int(sizeof(T)), kBufferFlags);
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo.x, lo.y, hi.x, hi.y}, part,
+                                               (rl * D + e0) * int(sizeof(T)), 0,
+                                               MERGE ? kAgentScope : 0);
       }
-      *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
   }
 
   // ---- the last split of a row block to finish combines all of its splits
-  if (it.merge >= 0 && a.merge_in_kernel) {
-    // release this split's partial at agent scope (every wavefront: its stores are
-    // written back past the L2 of its XCD before the barrier)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  if constexpr (MERGE) {
+    if (it.merge < 0 || !a.merge_in_kernel) return;
+    // every wavefront's stores have arrived before the barrier, and the count after it
+    const MergeGroup mg = a.merges[it.merge];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-      // system scope: the splits of a row block may run on different XCDs, whose
-      // L2 caches are not coherent with each other; a system-scope atomic is
-      // performed past them
-      const int old = __hip_atomic_fetch_add(a.counters + it.merge, 1, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_SYSTEM);
-      s_last = (old == a.merges[it.merge].nsplit - 1) ? 1 : 0;
+      // counts modulo the number of splits: zero again for the next launch
+      const unsigned last = unsigned(mg.nsplit - 1);
+      s_last = atomicInc(a.counters + it.merge, last) == last;
     }
     __syncthreads();
-    if (s_last) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the other splits' partials
-      const MergeGroup mg = a.merges[it.merge];
-      merge_rows<T, D>(mg, 0, mg.nrows, a.part_o, a.part_lse, a.RB, a.Hq, G, S, a.out, a.lse,
-                       tid, NT);
-      if (tid == 0)                        // ready for the next launch
-        __hip_atomic_store(a.counters + it.merge, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (s_last) merge_splits<T, D, NT>(mg, a, reinterpret_cast<float*>(sbuf), tid);
   }
 }
 
@@ -1730,21 +1829,35 @@ T* at_mut(void* base, size_t off) {
 }
 
 template <typename T, int D, int SRC>
-hipError_t launch_attn_t(const AttnParams& ap, int n_items, int rows, hipStream_t st,
-                         hipEvent_t e0, hipEvent_t e1) {
-  if (rows == 64)
-    return launch(reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256>), dim3(n_items),
-                  dim3(256), st, ap, e0, e1);
-  const void* k = rows == 256 ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 1, 512>)
-                              : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 512>);
-  return launch(k, dim3(n_items), dim3(512), st, ap, e0, e1);
+hipError_t launch_attn_t(const Plan& p, const AttnParams& ap, hipStream_t st, hipEvent_t e0,
+                         hipEvent_t e1) {
+  const dim3 grid(static_cast<unsigned>(p.items.size()));
+  const bool merge = p.merge_in_kernel;
+  if (p.rows_per_block == 64) {
+    // the 64-row kernel over bf16 pages (decode) is built with the merge only, and
+    // skips it where the plan merges apart: without it the compiler spills four
+    // registers there (decode at 128k 96.8 -> 101.0 us)
+    constexpr bool kAlways = SRC == SRC_PAGED && sizeof(T) == 2 && D == 128;
+    const void* k =
+        merge || kAlways ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, true>)
+                         : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, kAlways>);
+    return launch(k, grid, dim3(256), st, ap, e0, e1);
+  }
+  const void* k;
+  if (p.rows_per_block == 256)
+    k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 1, 512, true>)
+              : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 1, 512, false>);
+  else
+    k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 512, true>)
+              : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 512, false>);
+  return launch(k, grid, dim3(512), st, ap, e0, e1);
 }
 
 template <typename T, int SRC>
-hipError_t launch_attn_d(int D, const AttnParams& ap, int n, int rows, hipStream_t st,
-                         hipEvent_t e0, hipEvent_t e1) {
-  return D == 64 ? launch_attn_t<T, 64, SRC>(ap, n, rows, st, e0, e1)
-                 : launch_attn_t<T, 128, SRC>(ap, n, rows, st, e0, e1);
+hipError_t launch_attn_d(const Plan& p, const AttnParams& ap, hipStream_t st, hipEvent_t e0,
+                         hipEvent_t e1) {
+  return p.cfg.head_dim == 64 ? launch_attn_t<T, 64, SRC>(p, ap, st, e0, e1)
+                              : launch_attn_t<T, 128, SRC>(p, ap, st, e0, e1);
 }
 
 }  // namespace
@@ -1776,7 +1889,7 @@ hipError_t launch_attention(const Plan& p, void* ws, int src_kind, const void* k
   ap.block_table = at<int>(ws, p.ws.block_table);
   ap.items = at<WorkItem>(ws, p.ws.items);
   ap.merges = at<MergeGroup>(ws, p.ws.merges);
-  ap.counters = at_mut<int>(ws, p.ws.counters);
+  ap.counters = at_mut<unsigned>(ws, p.ws.counters);
   ap.k = k;
   ap.v = v;
   ap.k_scale = k_scale;
@@ -1788,22 +1901,19 @@ hipError_t launch_attention(const Plan& p, void* ws, int src_kind, const void* k
   ap.lse = lse;
   ap.part_o = at_mut<unsigned char>(ws, p.ws.part_o);
   ap.part_lse = at_mut<float>(ws, p.ws.part_lse);
-  const int n = static_cast<int>(p.items.size());
-  const int rows = p.rows_per_block;      // selects the row-block shape
-  const int D = p.cfg.head_dim;
   // a SIF plan has no cached tiles: its kernels never read k / v, whatever they are
   if (p.sif_n > 0) {
     if (p.cfg.act_dtype == C2KV_F32)
-      return launch_attn_d<float, SRC_PAGED_SIF>(D, ap, n, rows, st, e0, e1);
-    return launch_attn_d<__bf16, SRC_PAGED_SIF>(D, ap, n, rows, st, e0, e1);
+      return launch_attn_d<float, SRC_PAGED_SIF>(p, ap, st, e0, e1);
+    return launch_attn_d<__bf16, SRC_PAGED_SIF>(p, ap, st, e0, e1);
   }
   if (p.cfg.act_dtype == C2KV_F32) {
-    if (src_kind == SRC_PAGED) return launch_attn_d<float, SRC_PAGED>(D, ap, n, rows, st, e0, e1);
-    return launch_attn_d<float, SRC_POOL>(D, ap, n, rows, st, e0, e1);
+    if (src_kind == SRC_PAGED) return launch_attn_d<float, SRC_PAGED>(p, ap, st, e0, e1);
+    return launch_attn_d<float, SRC_POOL>(p, ap, st, e0, e1);
   }
-  if (src_kind == SRC_PAGED) return launch_attn_d<__bf16, SRC_PAGED>(D, ap, n, rows, st, e0, e1);
-  if (src_kind == SRC_POOL) return launch_attn_d<__bf16, SRC_POOL>(D, ap, n, rows, st, e0, e1);
-  return launch_attn_d<__bf16, SRC_POOL_I8>(D, ap, n, rows, st, e0, e1);
+  if (src_kind == SRC_PAGED) return launch_attn_d<__bf16, SRC_PAGED>(p, ap, st, e0, e1);
+  if (src_kind == SRC_POOL) return launch_attn_d<__bf16, SRC_POOL>(p, ap, st, e0, e1);
+  return launch_attn_d<__bf16, SRC_POOL_I8>(p, ap, st, e0, e1);
 }
 
 hipError_t launch_merge(const Plan& p, void* ws, void* out, float* lse, hipStream_t st,

@@ -50,6 +50,11 @@ constexpr int32_t kMinPiece = 2;      // shortest piece of a row block cut by sl
 // left the attention at 107-108 us and added a merge of 4-7 us).
 constexpr double kCutGain = 0.95;
 
+// Row blocks merged inside the attention kernel: splits, and bytes of their partials
+// where no other round of items hides it.
+constexpr int32_t kFewSplits = 5;
+constexpr int64_t kFewMergeBytes = 48 << 10;
+
 // A work list: items, by the XCD that runs them, and the row blocks to merge.
 struct Work {
   std::vector<WorkItem> items;
@@ -65,12 +70,22 @@ struct Work {
     n_partials += ns;
     return static_cast<int32_t>(merges.size()) - 1;
   }
-  // heaviest items first
-  void sort_queues() {
+  // the grid's order: each XCD's items heaviest first, the XCDs interleaved
+  void order() {
     for (auto& q : queue)
       std::stable_sort(q.begin(), q.end(), [](const WorkItem& a, const WorkItem& b) {
         return (a.tile1 - a.tile0) > (b.tile1 - b.tile0);
       });
+    std::vector<size_t> head(kXcds, 0);
+    for (size_t n = 0; n < items.size(); ++n) {
+      int x = static_cast<int>(n % kXcds);
+      if (head[x] >= queue[x].size()) {           // this queue ran dry: take the fullest one
+        size_t best = 0;
+        for (int y = 0; y < kXcds; ++y)
+          if (queue[y].size() - head[y] > best) { best = queue[y].size() - head[y]; x = y; }
+      }
+      items[n] = queue[x][head[x]++];
+    }
   }
 };
 
@@ -520,22 +535,20 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     }
     return wk;
   };
-  // Time of a work list in key tiles: the busiest XCD's slots, filled longest item
-  // first, and the merge (its launch, and its partials written and read).
-  auto makespan = [&](Work& wk) {
-    const int64_t slots = std::max<int64_t>(1, target / kXcds);
+  // Time of a work list in key tiles: each XCD's slots taken in the grid's order, and
+  // the merge (its launch, and its partials written and read).
+  auto makespan = [&](const Work& wk) {
+    const size_t slots = static_cast<size_t>(std::max<int64_t>(1, target / kXcds));
     double worst = 0;
-    for (auto& q : wk.queue) {
+    for (size_t x = 0; x < size_t(kXcds); ++x) {
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
-      int64_t last = 0;
-      for (const WorkItem& w : q) {
+      for (size_t n = x; n < wk.items.size(); n += kXcds) {
         int64_t at = 0;
-        if (int64_t(free_at.size()) == slots) { at = free_at.top(); free_at.pop(); }
-        at += w.tile1 - w.tile0 + kItemTiles;
-        last = std::max(last, at);
+        if (free_at.size() == slots) { at = free_at.top(); free_at.pop(); }
+        at += wk.items[n].tile1 - wk.items[n].tile0 + kItemTiles;
+        worst = std::max(worst, double(at));
         free_at.push(at);
       }
-      worst = std::max(worst, double(last));
     }
     if (!wk.merges.empty())
       worst += kMergeTiles;
@@ -544,35 +557,36 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
                (cfg.act_dtype == C2KV_F32 ? 4 : 2) / kTileBytes;
     return worst;
   };
-  even_splits.sort_queues();
+  even_splits.order();
   Work* work = &even_splits;
   Work by_slot;
   if (!sif && o.kv_splits == 0) {
     by_slot = cut_by_slot();
-    by_slot.sort_queues();
+    by_slot.order();
     if (makespan(by_slot) < kCutGain * makespan(even_splits) &&
         (layout(by_slot).total <= C2KV_STATIC_SCRATCH_BYTES ||
          layout(even_splits).total > C2KV_STATIC_SCRATCH_BYTES))
       work = &by_slot;
   }
-  // never chosen automatically: each split's agent-scope release writes back its
-  // XCD's whole L2 and the last split's acquire invalidates it, which costs the
-  // other workgroups there their cached keys and values (measured 2-5x slower
-  // than the separate merge kernel)
-  p.merge_in_kernel = o.merge_mode == 1;
+  // The last split of a row block to finish merges it where that takes one workgroup
+  // little (few splits), and either other workgroups run meanwhile (more than one
+  // round of items) or the partials are few bytes.  Else it is a tail that one
+  // workgroup per row block runs alone, and a separate launch spreads the rows over the
+  // machine.  Measured, separate kernel -> in the attention kernel: 143 row blocks of
+  // 256 rows in 2-3 splits 41.0 -> 36.6 us, decode batch of 24 in 4 splits
+  // 76.8 -> 75.6, 96 decode row blocks in 4 splits (one round) 9.9 -> 9.1; but 84 blocks of
+  // 64 rows in 5 splits, one round, 28.0 -> 29.2, 18 splits of 256 rows 16.0 -> 33.3.
+  int64_t merge_bytes = 0;
+  for (const MergeGroup& m : work->merges)
+    merge_bytes = std::max(merge_bytes, int64_t(m.nsplit) * m.nrows * D *
+                                            (cfg.act_dtype == C2KV_F32 ? 4 : 2));
+  p.merge_in_kernel =
+      o.merge_mode == 1 ||
+      (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
+       (int64_t(work->items.size()) > target || merge_bytes <= kFewMergeBytes));
 
-  // the grid interleaves the XCDs' queues
-  std::vector<size_t> head(kXcds, 0);
-  for (size_t n = 0; n < work->items.size(); ++n) {
-    int x = static_cast<int>(n % kXcds);
-    if (head[x] >= work->queue[x].size()) {     // this queue ran dry: take the fullest one
-      size_t best = 0;
-      for (int y = 0; y < kXcds; ++y)
-        if (work->queue[y].size() - head[y] > best) { best = work->queue[y].size() - head[y]; x = y; }
-    }
-    p.items.push_back(work->queue[x][head[x]++]);
-  }
   p.ws = layout(*work);
+  p.items = std::move(work->items);
   p.merges = std::move(work->merges);
   p.n_partials = work->n_partials;
   p.max_splits = work->max_splits;

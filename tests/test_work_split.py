@@ -35,11 +35,11 @@ CASES = [
     (dict(batch=5, n_q_heads=8, n_kv_heads=2, suffix_len=29, chunks_per_req=4, chunk_len=400,
           pool_dtype="i8"), 8),
     # 256-row blocks, the last of a request short, head_dim 64
-    (dict(batch=3, n_q_heads=12, n_kv_heads=4, suffix_len=101, chunks_per_req=4, chunk_len=500,
-          head_dim=64), 16),
+    (dict(batch=5, n_q_heads=12, n_kv_heads=4, suffix_len=101, chunks_per_req=4, chunk_len=500,
+          head_dim=64), 32),
     # fp32
     (dict(batch=3, n_q_heads=4, n_kv_heads=4, suffix_len=70, chunks_per_req=4, chunk_len=500,
-          pool_dtype="f32"), 16),
+          pool_dtype="f32"), 24),
 ]
 
 
