@@ -235,7 +235,7 @@ __device__ inline uint4 keep_first(uint4 v, int n_keep) {
 // ----------------------------------------------------------------------------
 
 struct AttnParams {
-  int Hq, Hkv, G, S, PS, max_pages, RB, n_seg, merge_in_kernel;
+  int Hq, Hkv, G, S, PS, max_pages, RB, n_seg;
   int sif_n, sif_block, sif_sink;  // SIF mask over the suffix when sif_n > 0
   int tpp;                      // key tiles per page (PS / KT)
   unsigned tpp_magic;           // floor(2^32 / tpp) + 1 (tpp > 1)
@@ -297,6 +297,8 @@ struct Lds {
   static constexpr int LDK = D + 16 / int(sizeof(T));
   static constexpr int LDV = KT + (sizeof(T) == 2 ? 16 : 8) / int(sizeof(T));
   static constexpr int TILE = KT * LDK + D * LDV;   // elements of one stage
+  // column `col` of row `d` where the rows' 8-element blocks are permuted (kRowV)
+  __device__ static constexpr int vswap(int d, int col) { return col ^ (8 * ((d >> 4) & 7)); }
   // column of key k in a transposed value row (swaps bits 2 and 3 of k for bf16)
   __device__ static constexpr int vcol(int k) {
     return sizeof(T) == 2 ? (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1) : k;
@@ -519,10 +521,19 @@ struct TileLoader {
   using L = Lds<T, D>;
   static constexpr int HALF = D / 2;
   static constexpr int KUPK = D / 16;       // key units per key
+  // Value units of bf16 tiles that are gathered by row: consecutive threads take the
+  // consecutive chunks of a key pair's rows, so that a load reads whole rows (4 key
+  // pairs' rows a wavefront at D = 128) and a pair's int8 scales are one address.  A
+  // wavefront's transposed words then lie in few columns of many rows: the 16-byte
+  // blocks of a value row are permuted by its index / 16 (vblock), which spreads them
+  // over the banks and leaves the fragments' reads of 16 rows conflict-free.  (Kernels
+  // over pages copy their transposed rows and keep a pair's chunks on one thread column.)
+  // With a pair's chunks on 16 threads of eight wavefronts, every load touched 64 cache
+  // lines: int8 layer 23.2 -> 21.6 us, int8 ragged batch 126.5 -> 121.1 us.
+  static constexpr bool kRowV = sizeof(T) == 2 && SRC != SRC_PAGED;
 
   const AttnParams& a;
   const int tid, b, g, S, slot0, N, nct, page0;
-  const int kp2;                            // first of the two keys of this thread's value units
   const T* ksuf;
   const T* vsuf;
   const PoolT* kpool;
@@ -533,17 +544,30 @@ struct TileLoader {
   float ck[Sh::NKU][8], sk[Sh::NKU][8];     // cos/sin of this thread's key units
   int cs_seg[Sh::NKU];                      // segment the pool cos/sin belong to
   int2 nk[Sh::NKU];                         // (row, segment) of the next tile's keys
-  int nv[2];                                // pool rows of its values (only the row: a
+  int nv[Sh::NVU][2];                       // pool rows of its values (only the row: a
                                             // loaded word left unused would be reused
                                             // while its load is in flight)
-  uint32_t kofs[Sh::NPK], vofs[Sh::NPV];    // paged: byte offsets of this thread's vectors
-  float k_scale[Sh::NKU], v_scale[2];
+  // paged: byte offsets of this thread's vectors.  Loops that load every tile they ask
+  // for keep the first vector's only and step in the loads' scalar offset (six registers
+  // less in the 64-row kernel, which is at its limit); two-set loops, whose descriptors
+  // may have no extent, keep the whole offset where it is checked against it.
+  static constexpr bool kStep = !(NT == 512 && sizeof(T) == 2);
+  uint32_t kofs[kStep ? 1 : Sh::NPK], vofs[kStep ? 1 : Sh::NPV];
+  float k_scale[Sh::NKU], v_scale[Sh::NVU][2];
+
+  // chunk and first key of value unit i of this thread
+  __device__ __forceinline__ int vchunk(int i) const {
+    const int u = tid + i * NT;
+    return kRowV ? u % (D / 8) : u / (KT / 2);
+  }
+  __device__ __forceinline__ int vkey(int i) const {
+    return kRowV ? 2 * ((tid + i * NT) / (D / 8)) : 2 * (tid % (KT / 2));
+  }
 
   __device__ __forceinline__ TileLoader(const AttnParams& a_, int tid_, int b_, int g_, int slot0_,
                                         int N_, int page0_)
       : a(a_), tid(tid_), b(b_), g(g_), S(a_.S), slot0(slot0_), N(N_), nct((N_ + KT - 1) / KT),
-        page0(page0_),
-        kp2(2 * (tid_ % (KT / 2))), ksuf(static_cast<const T*>(a_.k_suf)),
+        page0(page0_), ksuf(static_cast<const T*>(a_.k_suf)),
         vsuf(static_cast<const T*>(a_.v_suf)), kpool(static_cast<const PoolT*>(a_.k)),
         vpool(static_cast<const PoolT*>(a_.v)) {
 #pragma unroll
@@ -552,21 +576,24 @@ struct TileLoader {
       cs_seg[i] = -1;
       k_scale[i] = 1.f;
     }
-    nv[0] = nv[1] = 0;
+#pragma unroll
+    for (int i = 0; i < Sh::NVU; ++i) {
+      nv[i][0] = nv[i][1] = 0;
+      v_scale[i][0] = v_scale[i][1] = 1.f;
+    }
     if constexpr (kPaged) {
       constexpr int EPV = Sh::EPV;
 #pragma unroll
-      for (int i = 0; i < Sh::NPK; ++i) {
+      for (int i = 0; i < (kStep ? 1 : Sh::NPK); ++i) {
         const int u = tid + i * NT;
         kofs[i] = uint32_t((u / (D / EPV)) * D + (u % (D / EPV)) * EPV) * sizeof(T);
       }
 #pragma unroll
-      for (int i = 0; i < Sh::NPV; ++i) {
+      for (int i = 0; i < (kStep ? 1 : Sh::NPV); ++i) {
         const int u = tid + i * NT;
         vofs[i] = uint32_t((u / (KT / EPV)) * a.PS + (u % (KT / EPV)) * EPV) * sizeof(T);
       }
     }
-    v_scale[0] = v_scale[1] = 1.f;
   }
 
   // Every load here and in fetch_data is unconditional, from a clamped index
@@ -594,9 +621,10 @@ struct TileLoader {
         nk[i] = a.slot_info[slot0 + k0 + min(kk, nvalid - 1)];
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        nv[j] = a.slot_info[slot0 + k0 + min(kp2 + j, nvalid - 1)].x;
-      }
+      for (int i = 0; i < (kRowV ? Sh::NVU : 1); ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          nv[i][j] = a.slot_info[slot0 + k0 + min(vkey(i) + j, nvalid - 1)].x;
     }
   }
 
@@ -624,12 +652,18 @@ struct TileLoader {
                   "every thread loads whole page vectors");
 #pragma unroll
     for (int i = 0; i < Sh::NPK; ++i) {
-      const auto val = __builtin_amdgcn_raw_buffer_load_b128(kr, kofs[i], 0, 0);
+      const auto val =
+          kStep ? __builtin_amdgcn_raw_buffer_load_b128(kr, kofs[0], i * NT * 16, 0)
+                : __builtin_amdgcn_raw_buffer_load_b128(kr, kofs[kStep ? 0 : i], 0, 0);
       K[4 * i] = val[0]; K[4 * i + 1] = val[1]; K[4 * i + 2] = val[2]; K[4 * i + 3] = val[3];
     }
 #pragma unroll
     for (int i = 0; i < Sh::NPV; ++i) {
-      const auto val = __builtin_amdgcn_raw_buffer_load_b128(vr, vofs[i], 0, 0);
+      const int rows = i * (NT / (KT / Sh::EPV));        // value rows of i vectors a thread
+      const auto val =
+          kStep ? __builtin_amdgcn_raw_buffer_load_b128(vr, vofs[0],
+                                                        rows * a.PS * int(sizeof(T)), 0)
+                : __builtin_amdgcn_raw_buffer_load_b128(vr, vofs[kStep ? 0 : i], 0, 0);
       V[4 * i] = val[0]; V[4 * i + 1] = val[1]; V[4 * i + 2] = val[2]; V[4 * i + 3] = val[3];
     }
   }
@@ -693,12 +727,12 @@ struct TileLoader {
 #pragma unroll
       for (int i = 0; i < Sh::NVU; ++i) {
         const int u = tid + i * NT;
-        const int c = u / (KT / 2);
+        const int c = vchunk(i);
         uint32_t* w = rv + i * 2 * Sh::WA;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           if (Sh::VU_ALL || u < Sh::VU_TOT) {
-            const size_t row = (size_t(b) * S + k0 + min(kp2 + j, nvalid - 1)) * a.Hkv + g;
+            const size_t row = (size_t(b) * S + k0 + min(vkey(i) + j, nvalid - 1)) * a.Hkv + g;
             raw_load8<T>(w + j * Sh::WA, vsuf + row * D + 8 * c);
           }
         }
@@ -713,14 +747,14 @@ struct TileLoader {
 #pragma unroll
       for (int i = 0; i < Sh::NVU; ++i) {
         const int u = tid + i * NT;
-        const int c = u / (KT / 2);
+        const int c = vchunk(i);
         uint32_t* w = rv + i * 2 * Sh::WP;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           if (Sh::VU_ALL || u < Sh::VU_TOT) {
-            const size_t row = size_t(nv[j]) * a.Hkv + g;
+            const size_t row = size_t(nv[kRowV ? i : 0][j]) * a.Hkv + g;
             raw_load8<PoolT>(w + j * Sh::WP, vpool + row * D + 8 * c);
-            if constexpr (SRC == SRC_POOL_I8) v_scale[j] = a.v_scale[row];
+            if constexpr (SRC == SRC_POOL_I8) v_scale[i][j] = a.v_scale[row];
           }
         }
       }
@@ -784,16 +818,18 @@ struct TileLoader {
       for (int i = 0; i < Sh::NVU; ++i) {
         const int u = tid + i * NT;
         if (!Sh::VU_ALL && u >= Sh::VU_TOT) continue;
-        const int c = u / (KT / 2);
+        const int c = vchunk(i);
+        // rows 8c .. 8c + 7 share a block permutation
+        T* const col = sV + (kRowV ? L::vswap(8 * c, L::vcol(vkey(i))) : L::vcol(vkey(i)));
         // bf16 values that need no decode: a transposed word holds element e of
-        // the two keys kp2 and kp2 + 1, i.e. one 16-bit half of each row's word
+        // the unit's two keys, i.e. one 16-bit half of each row's word
         constexpr bool kRawV = sizeof(T) == 2 && !(from_pool && SRC == SRC_POOL_I8);
         if (kRawV) {
           const uint32_t* w0 = rv + i * 2 * (from_pool ? Sh::WP : Sh::WA);
           const uint32_t* w1 = w0 + (from_pool ? Sh::WP : Sh::WA);
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            T* dst = sV + (8 * c + e) * L::LDV + L::vcol(kp2);
+            T* dst = col + (8 * c + e) * L::LDV;
             *reinterpret_cast<uint32_t*>(dst) =
                 __builtin_amdgcn_perm(w1[e / 2], w0[e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
           }
@@ -807,7 +843,7 @@ struct TileLoader {
             raw_to_f8<PoolT>(w + Sh::WP, x1);
             if constexpr (SRC == SRC_POOL_I8) {
 #pragma unroll
-              for (int e = 0; e < 8; ++e) { x0[e] *= v_scale[0]; x1[e] *= v_scale[1]; }
+              for (int e = 0; e < 8; ++e) { x0[e] *= v_scale[i][0]; x1[e] *= v_scale[i][1]; }
             }
           }
         } else {
@@ -818,7 +854,7 @@ struct TileLoader {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float a0 = x0[e], a1 = x1[e];
-          T* dst = sV + (8 * c + e) * L::LDV + L::vcol(kp2);
+          T* dst = col + (8 * c + e) * L::LDV;
           if constexpr (sizeof(T) == 2) {
             *reinterpret_cast<uint32_t*>(dst) = pack_bf16(a0, a1);
           } else {
@@ -1173,6 +1209,12 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   // ---- O^T += V^T P^T; chunk c of the tile covers keys 16*(c%2) + 4*half +
   // {0..3} and + 8 + {0..3} of block c / 2 (bf16: one 16-byte read at column
   // 16*(c%2) + 8*half of the block's permuted row)
+  // (element column of chunk c in row db * 32 + qi: block 2c + half, permuted where the
+  // loader permutes by row / 16 = 2 db + qi / 16)
+  auto vcol_of = [&](int c, int db) __attribute__((always_inline)) {
+    if constexpr (TileLoader<T, D, SRC, NT>::kRowV) return 16 * (c ^ db) + 8 * (half ^ (qi >> 4));
+    else return 16 * c + 8 * half;
+  };
   auto pv = [&](const T* sV, const Op (&pb)[NPW]) {
     if constexpr (KPL == 8 && kPaged) {
       // value fragments in a ring of AH ahead of their MFMAs, as for the keys
@@ -1180,7 +1222,7 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       auto frag = [&](int f) {
         const int cc = f / NDB, db = f % NDB;
         const int c = kh * NPW + cc;
-        const T* vrow = sV + (db * 32 + qi) * L::LDV + (c / CPB) * 32 + 8 * half + 16 * (c % CPB);
+        const T* vrow = sV + (db * 32 + qi) * L::LDV + vcol_of(c, db);
         return *reinterpret_cast<const Op*>(vrow);
       };
       Op vf[AH];
@@ -1197,11 +1239,9 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 #pragma unroll
       for (int cc = 0; cc < NPW; ++cc) {
         const int c = kh * NPW + cc;
-        const int kb = c / CPB;
-        const int kofs = 16 * (c % CPB);
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
-          const T* vrow = sV + (db * 32 + qi) * L::LDV + kb * 32 + 8 * half + kofs;
+          const T* vrow = sV + (db * 32 + qi) * L::LDV + vcol_of(c, db);
           o[db] = M::run(*reinterpret_cast<const Op*>(vrow), pb[cc], o[db]);
         }
       }
@@ -1269,6 +1309,13 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
     }
   };
 
+  // Wavefronts 4-7 of a 512-thread workgroup (the second on each SIMD) prepare the next
+  // tile after this one's products, the others before them: with all eight in one order,
+  // a tile cost its loader's VALU work, then its products and softmax, one after the
+  // other (ragged batch 117.1 -> 110.4 us, int8 layer 24.1 -> 23.2).  Not for fp32, whose
+  // loader is little beside its products and whose 256-row kernels spill.
+  const bool late = NT == 512 && sizeof(T) == 2 && __builtin_amdgcn_readfirstlane(wave) >= 4;
+
   // in the paged loop below, a wavefront whose row group is empty (decode: 4
   // rows in a 128-row block) still loads and commits its share of each tile
   // but computes nothing
@@ -1319,12 +1366,16 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       for (int i = ta; i < tb; ++i) {
         const int stage = (i - ta) & 1;
         // next tile into the other stage; its readers finished before the last barrier
-        if (i + 1 < tb) {
-          ld.template commit<SUF>(tile_of(i + 1), kst(stage ^ 1), vst(stage ^ 1));
-          if (i + 2 < tb) ld.template fetch_data<SUF>(tile_of(i + 2));
-          if (i + 3 < tb) ld.template fetch_idx<SUF>(tile_of(i + 3));
-        }
+        auto next = [&]() __attribute__((always_inline)) {
+          if (i + 1 < tb) {
+            ld.template commit<SUF>(tile_of(i + 1), kst(stage ^ 1), vst(stage ^ 1));
+            if (i + 2 < tb) ld.template fetch_data<SUF>(tile_of(i + 2));
+            if (i + 3 < tb) ld.template fetch_idx<SUF>(tile_of(i + 3));
+          }
+        };
+        if (!late) next();
         tile_compute(tile_of(i), stage);
+        if (late) next();
         __syncthreads();   // next stage written; this stage free for the tile after next
       }
     }
@@ -1428,7 +1479,7 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 
   // ---- the last split of a row block to finish combines all of its splits
   if constexpr (MERGE) {
-    if (it.merge < 0 || !a.merge_in_kernel) return;
+    if (it.merge < 0) return;
     // every wavefront's stores have arrived before the barrier, and the count after it
     const MergeGroup mg = a.merges[it.merge];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1834,13 +1885,8 @@ hipError_t launch_attn_t(const Plan& p, const AttnParams& ap, hipStream_t st, hi
   const dim3 grid(static_cast<unsigned>(p.items.size()));
   const bool merge = p.merge_in_kernel;
   if (p.rows_per_block == 64) {
-    // the 64-row kernel over bf16 pages (decode) is built with the merge only, and
-    // skips it where the plan merges apart: without it the compiler spills four
-    // registers there (decode at 128k 96.8 -> 101.0 us)
-    constexpr bool kAlways = SRC == SRC_PAGED && sizeof(T) == 2 && D == 128;
-    const void* k =
-        merge || kAlways ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, true>)
-                         : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, kAlways>);
+    const void* k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, true>)
+                          : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, false>);
     return launch(k, grid, dim3(256), st, ap, e0, e1);
   }
   const void* k;
@@ -1877,7 +1923,6 @@ hipError_t launch_attention(const Plan& p, void* ws, int src_kind, const void* k
   ap.max_pages = p.max_pages;
   ap.RB = p.rows_per_block;
   ap.n_seg = p.n_segments;
-  ap.merge_in_kernel = p.merge_in_kernel ? 1 : 0;
   ap.sif_n = p.sif_n;
   ap.sif_block = p.sif_block;
   ap.sif_sink = p.sif_sink;
