@@ -1728,17 +1728,25 @@ __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
 // then all rows and cos/sin, then the turned keys and the transposed values
 // (through LDS) are written.  Loads are unconditional (indices clamped into the
 // tile); keys and values past the tile's end are written as zeros.
+//
+// Bound by HBM.  Values are read a key pair's whole rows at a time (consecutive
+// threads, consecutive chunks) and transposed as words of two keys; the 16-byte blocks
+// of an LDS row are permuted by its index / 16, so that the writes, few columns of many
+// rows, fall on all banks.
 template <typename T, int D, typename PoolT>
 __global__ __launch_bounds__(256) void compose_kernel(ComposeParams a) {
-  using L = Lds<T, D>;
   constexpr int NTH = 256;
   constexpr int KU = D / 16;                 // key units per key: 8-element pairs (c, c + D/2)
   constexpr int NKU = KT * KU / NTH;         // key units per thread
-  constexpr int VU = D / 8;                  // value units per key: 8 elements
-  constexpr int NVU = KT * VU / NTH;         // value units per thread (one key: tid % KT)
-  static_assert(KT * KU % NTH == 0 && KT * VU % NTH == 0 && NTH % KT == 0,
-                "every thread holds whole units of one value key");
-  __shared__ __attribute__((aligned(16))) T sV[D * L::LDV];
+  constexpr int VU = D / 8;                  // value units per key pair: 8 elements of both
+  constexpr int NVU = KT / 2 * VU / NTH;     // value units per thread
+  constexpr int EPV = 16 / sizeof(T);        // elements per 16-byte block
+  constexpr int LDV = KT + EPV;              // LDS row of a value element
+  static_assert(KT * KU % NTH == 0 && KT / 2 * VU % NTH == 0,
+                "every thread holds whole units");
+  __shared__ __attribute__((aligned(16))) T sV[D * LDV];
+  // column `col` of row d (a row holds 8 blocks of bf16, 16 of fp32)
+  auto vswap = [](int d, int col) { return col ^ (EPV * ((d >> 4) * (sizeof(T) == 4 ? 2 : 1))); };
   const int tid = threadIdx.x;
   const int4 tl = a.tiles[blockIdx.x];
   const int g = blockIdx.y;
@@ -1758,16 +1766,25 @@ __global__ __launch_bounds__(256) void compose_kernel(ComposeParams a) {
     ks[i] = a.slot_info[slot];
     kpos[i] = a.out_pos ? a.slot_pos[slot] : 0;
   }
-  const int vkk = tid % KT;
-  const int vsrc = a.slot_info[first + min(vkk, nvalid - 1)].x;
+  int vsrc[NVU][2];
+#pragma unroll
+  for (int i = 0; i < NVU; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      vsrc[i][j] = a.slot_info[first + min(2 * ((tid + i * NTH) / VU) + j, nvalid - 1)].x;
 
   // ---- rows, scales and cos/sin
-  float kx[NKU][8], ky[NKU][8], kc[NKU][8], kn[NKU][8], vx[NVU][8];
-  float kscale[NKU], vscale = 1.f;
-  const size_t vrow = size_t(vsrc) * a.Hkv + g;
+  float kx[NKU][8], ky[NKU][8], kc[NKU][8], kn[NKU][8], vx[NVU][2][8];
+  float kscale[NKU], vscale[NVU][2];
 #pragma unroll
-  for (int i = 0; i < NVU; ++i) load8(vpool + vrow * D + 8 * ((tid + i * NTH) / KT), vx[i]);
-  if constexpr (sizeof(PoolT) == 1) vscale = a.v_scale[vrow];
+  for (int i = 0; i < NVU; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const size_t row = size_t(vsrc[i][j]) * a.Hkv + g;
+      load8(vpool + row * D + 8 * ((tid + i * NTH) % VU), vx[i][j]);
+      vscale[i][j] = 1.f;
+      if constexpr (sizeof(PoolT) == 1) vscale[i][j] = a.v_scale[row];
+    }
 #pragma unroll
   for (int i = 0; i < NKU; ++i) {
     const int c = (tid + i * NTH) % KU;
@@ -1805,23 +1822,26 @@ __global__ __launch_bounds__(256) void compose_kernel(ComposeParams a) {
     }
   }
   // ---- values: decoded, transposed through LDS, then each d-row of the page segment
-  const bool vok = vkk < nvalid;
 #pragma unroll
   for (int i = 0; i < NVU; ++i) {
-    const int c = (tid + i * NTH) / KT;
+    const int c = (tid + i * NTH) % VU, kk = 2 * ((tid + i * NTH) / VU);
+    T* col = sV + vswap(8 * c, kk);            // rows 8c .. 8c + 7 share a permutation
+    const bool ok0 = kk < nvalid, ok1 = kk + 1 < nvalid;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      sV[(8 * c + e) * L::LDV + vkk] = from_f<T>(vok ? vx[i][e] * vscale : 0.f);
+    for (int e = 0; e < 8; ++e) {
+      const float x0 = ok0 ? vx[i][0][e] * vscale[i][0] : 0.f;
+      const float x1 = ok1 ? vx[i][1][e] * vscale[i][1] : 0.f;
+      T* dst = col + (8 * c + e) * LDV;
+      if constexpr (sizeof(T) == 2) *reinterpret_cast<uint32_t*>(dst) = pack_bf16(x0, x1);
+      else *reinterpret_cast<float2*>(dst) = make_float2(x0, x1);
+    }
   }
   __syncthreads();
-  constexpr int EPV = 16 / sizeof(T);
   constexpr int VV = KT / EPV;
   for (int u = tid; u < D * VV; u += NTH) {
     const int d = u / VV, vec = u % VV;
-    const uint2* src = reinterpret_cast<const uint2*>(sV + d * L::LDV + vec * EPV);
-    const uint2 lo = src[0], hi = src[1];     // LDS rows are 8-byte aligned
     *reinterpret_cast<uint4*>(vpage + size_t(d) * a.PS + vec * EPV) =
-        make_uint4(lo.x, lo.y, hi.x, hi.y);
+        *reinterpret_cast<const uint4*>(sV + d * LDV + vswap(d, vec * EPV));
   }
 }
 
