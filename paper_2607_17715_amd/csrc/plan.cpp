@@ -38,10 +38,12 @@ std::vector<double> rope_theta(int D, double base) {
 
 constexpr int kXcds = 8;
 
-// Costs in key tiles of a 256-row block, for choosing between work lists: what an
-// item costs beside its tiles, the launch of the merge, and the bytes of partials
-// that take as long as a tile.
+// Costs in bf16 key tiles of a 256-row block, for choosing between work lists: what an
+// item costs beside its tiles, the launch of the merge, the bytes of partials that take
+// as long as a tile, and an fp32 tile (its products: 13.7 us at 157 TFLOP/s, a bf16
+// tile 1.9 us).
 constexpr int64_t kItemTiles = 3;
+constexpr int64_t kF32TileCost = 7;
 constexpr double kMergeTiles = 2.0;
 constexpr double kTileBytes = 4e6;
 constexpr int32_t kMinPiece = 2;      // shortest piece of a row block cut by slot
@@ -490,6 +492,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // tiles on 256 CUs, which two equal splits each took in a full round and a
   // nearly empty one, 182 -> 135 us; 192 decode row blocks of 59 tiles in three
   // splits on 512 slots, 86.5 -> 73.6 us.
+  const int64_t tile_cost = cfg.act_dtype == C2KV_F32 ? kF32TileCost : 1;
   struct Piece { int32_t end; int64_t slot; };       // of a row block, from the last one's end
   std::vector<std::vector<Piece>> pieces;
   auto fill_slots = [&](int64_t load) {              // the number of slots taken
@@ -498,7 +501,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     for (size_t i = 0; i < groups.size(); ++i)
       for (int32_t t = 0; t < groups[i].tiles;) {
         const int32_t left = groups[i].tiles - t;
-        int64_t n = std::min<int64_t>(left, room - kItemTiles);
+        int64_t n = std::min<int64_t>(left, (room - kItemTiles) / tile_cost);
         if (n < left && left - n < kMinPiece) n = left - kMinPiece;
         if (int32_t(pieces[i].size()) == kMaxSplits - 1) n = left;
         if (n < std::min(left, kMinPiece)) {
@@ -507,15 +510,15 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
           continue;
         }
         t += static_cast<int32_t>(n);
-        room -= n + kItemTiles;
+        room -= n * tile_cost + kItemTiles;
         pieces[i].push_back({t, slot});
       }
     return slot + 1;
   };
   auto cut_by_slot = [&]() {
     Work wk;
-    int64_t lo = kItemTiles + 2 * kMinPiece;
-    int64_t hi = std::max(lo, total_tiles + kItemTiles * int64_t(groups.size()));
+    int64_t lo = kItemTiles + 2 * kMinPiece * tile_cost;
+    int64_t hi = std::max(lo, total_tiles * tile_cost + kItemTiles * int64_t(groups.size()));
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
       if (fill_slots(mid) <= target) hi = mid;
@@ -535,7 +538,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     }
     return wk;
   };
-  // Time of a work list in key tiles: each XCD's slots taken in the grid's order, and
+  // Time of a work list in bf16 key tiles: each XCD's slots taken in the grid's order, and
   // the merge (its launch, and its partials written and read).
   auto makespan = [&](const Work& wk) {
     const size_t slots = static_cast<size_t>(std::max<int64_t>(1, target / kXcds));
@@ -545,7 +548,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
       for (size_t n = x; n < wk.items.size(); n += kXcds) {
         int64_t at = 0;
         if (free_at.size() == slots) { at = free_at.top(); free_at.pop(); }
-        at += wk.items[n].tile1 - wk.items[n].tile0 + kItemTiles;
+        at += (wk.items[n].tile1 - wk.items[n].tile0) * tile_cost + kItemTiles;
         worst = std::max(worst, double(at));
         free_at.push(at);
       }
@@ -560,7 +563,10 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   even_splits.order();
   Work* work = &even_splits;
   Work by_slot;
-  if (!sif && o.kv_splits == 0) {
+  // Even splits that fit one round of slots are balanced to the rounding of a tile: only
+  // lists of more items are cut (24 fp32 row blocks of 256 rows, 4 to 16 tiles each, ran
+  // 60 us in pieces of one and two tiles and 99 us cut into pieces of up to four).
+  if (!sif && o.kv_splits == 0 && int64_t(even_splits.items.size()) > target) {
     by_slot = cut_by_slot();
     by_slot.order();
     if (makespan(by_slot) < kCutGain * makespan(even_splits) &&
