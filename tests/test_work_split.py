@@ -43,6 +43,16 @@ CASES = [
 ]
 
 
+def test_one_round_of_even_splits_is_kept():
+    """24 fp32 row blocks of 256 rows, 5 to 17 tiles each: pieces of one and two tiles fit one
+    round of 256 slots, so they are not cut into fewer and longer ones."""
+    w = synth.small(pool_dtype="f32", n_q_heads=8, n_kv_heads=2, batch=1, chunks_per_req=2,
+                    keep=("count", 130), prefix_len=0, suffix_len=744, seed=3)
+    i = c2kv.Plan.for_workload(w).info
+    assert i["rows_per_block"] == 256 and i["n_merge_groups"] == 24
+    assert 200 < i["n_work_items"] <= 256, i
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,num_cus", CASES)
 def test_cut_row_blocks_parity(shape, num_cus):
