@@ -376,16 +376,16 @@ __device__ inline float load_shared(const float* p) {
 // them at a time over batches of NB splits; with fewer (decode), the splits are also
 // spread over `lanes` sets of threads, combined through LDS (`xs`).  Bound by the
 // latency of the loads, which are all in flight within a batch.
-template <typename T, int D, int NT>
+template <typename T, typename PT, int D, int NT>
 __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnParams& a, float* xs,
                                              int tid) {
-  constexpr int EPT = 16 / int(sizeof(T));      // elements per chunk
+  constexpr int EPT = 16 / int(sizeof(PT));     // elements per chunk
   constexpr int CPR = D / EPT;                  // chunks per row
   const int units = mg.nrows * CPR, ns = mg.nsplit;
   const float* pl = a.part_lse + size_t(mg.part0) * a.RB;
   const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(
-      static_cast<T*>(a.part_o) + size_t(mg.part0) * a.RB * D, 0,
-      ns * a.RB * D * int(sizeof(T)), kBufferFlags);
+      static_cast<PT*>(a.part_o) + size_t(mg.part0) * a.RB * D, 0,
+      ns * a.RB * D * int(sizeof(PT)), kBufferFlags);
   auto store_row = [&](int u, float mx, float z, const float (&acc)[EPT])
       __attribute__((always_inline)) {
     const int rloc = u / CPR, e0 = (u % CPR) * EPT;
@@ -396,6 +396,9 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
     if constexpr (sizeof(T) == 4) {
       *reinterpret_cast<float4*>(dst) =
           make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    } else if constexpr (EPT == 4) {
+      *reinterpret_cast<uint2*>(dst) =
+          make_uint2(pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv));
     } else {
       float x[8];
 #pragma unroll
@@ -429,7 +432,7 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
           const int sp = min(i + j * istep, ns - 1);
           l[k][j] = load_shared(pl + size_t(sp) * a.RB + rloc);
           const auto x = __builtin_amdgcn_raw_buffer_load_b128(
-              po, ((sp * a.RB + rloc) * D + (u % CPR) * EPT) * int(sizeof(T)), 0, kAgentScope);
+              po, ((sp * a.RB + rloc) * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
           w[k][j][0] = x[0]; w[k][j][1] = x[1]; w[k][j][2] = x[2]; w[k][j][3] = x[3];
         }
       }
@@ -451,7 +454,7 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
         for (int j = 0; j < NB; ++j) {
           const float wt = __expf(l[k][j] - mr);
           z[k] += wt;
-          if constexpr (sizeof(T) == 4) {
+          if constexpr (sizeof(PT) == 4) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[k][e] += wt * __uint_as_float(w[k][j][e]);
           } else {
@@ -876,7 +879,8 @@ struct TileLoader {
 // to a CU, so that two work items' latencies overlap.  MERGE: the last split of a row
 // block merges it where the plan says so (kernels of their own: the merge raises the
 // registers of some, and SIF extraction measured 1.1 % slower with it behind a branch).
-template <typename T, int D, int SRC, int KG, int NT, bool MERGE>
+// PT: type of the partials (float where the plan holds them so: Plan::part_f32).
+template <typename T, typename PT, int D, int SRC, int KG, int NT, bool MERGE>
 __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   constexpr int NRG = NT / 64 / KG;         // row groups
   constexpr int NKB = 2 / KG;               // 32-key blocks per wavefront and tile
@@ -1416,63 +1420,110 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 
   // ---- epilogue: rows normalised and staged in LDS (accumulator value v of
   // block db holds d = 32*db + 8*(v/4) + 4*half + v%4), then copied out as
-  // whole rows: to the output, or in the activation dtype to the partials
+  // whole rows: to the output, or as PT to the partials
   const float l_tot = half_pair_sum(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   const float lse_val = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
-  constexpr int LDO = D + (sizeof(T) == 2 ? 4 : 2);   // staged row, 8-byte aligned
-  static_assert(NRG * 32 * LDO <= SBUF, "staged rows must fit in the tile stages");
-  if constexpr (KG == 2) __syncthreads();   // the key-half exchange is read before reuse
-  if (writer) {
-    T* srow = sbuf + (rgrp * 32 + qi) * LDO;
+  if (!std::is_same<T, PT>::value && it.partial >= 0) {
+    // fp32 partials beside bf16 tiles, in passes of as many row groups as both tile stages
+    // hold (256 rows take two)
+    constexpr int LDF = D + 2;                           // staged row, 8-byte aligned
+    constexpr int GPP = NRG * 32 * LDF * 4 <= SBUF * int(sizeof(T)) ? NRG : NRG / 2;
+    static_assert(sizeof(T) == sizeof(PT) || GPP * 32 * LDF * 4 <= SBUF * int(sizeof(T)),
+                  "staged rows must fit in the tile stages");
+    float* const sout = reinterpret_cast<float*>(sbuf);
+    const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<float*>(a.part_o) + size_t(it.partial) * a.RB * D, 0, a.RB * D * 4,
+        kBufferFlags);
+    if (writer && row_ok && half == 0) {
+      float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
+      if constexpr (MERGE)
+        __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        *dst = lse_val;
+    }
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int g0 = 0; g0 < NRG; g0 += GPP) {
+      // the key-half exchange, or the rows of the pass before, are read before reuse
+      if (KG == 2 || g0 > 0) __syncthreads();
+      if (writer && rgrp / GPP == g0 / GPP) {
+        float* srow = sout + (rgrp % GPP * 32 + qi) * LDF;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int d = 32 * db + 8 * i + 4 * half;
-        const float x0 = o[db][4 * i] * inv, x1 = o[db][4 * i + 1] * inv;
-        const float x2 = o[db][4 * i + 2] * inv, x3 = o[db][4 * i + 3] * inv;
-        if constexpr (sizeof(T) == 4) {
-          reinterpret_cast<float2*>(srow + d)[0] = make_float2(x0, x1);
-          reinterpret_cast<float2*>(srow + d)[1] = make_float2(x2, x3);
-        } else {
-          *reinterpret_cast<uint2*>(srow + d) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
-        }
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float2* dst = reinterpret_cast<float2*>(srow + 32 * db + 8 * i + 4 * half);
+            dst[0] = make_float2(o[db][4 * i] * inv, o[db][4 * i + 1] * inv);
+            dst[1] = make_float2(o[db][4 * i + 2] * inv, o[db][4 * i + 3] * inv);
+          }
       }
-    if (row_ok && half == 0) {
-      if (it.partial < 0) {
-        if (a.lse) a.lse[(size_t(b) * a.Hq + h) * S + t] = lse_val;
-      } else {
-        float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
-        if constexpr (MERGE)
-          __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-          *dst = lse_val;
+      __syncthreads();
+      const int nrows = min(GPP * 32, it.nrows - g0 * 32);
+      for (int ch = tid; ch < nrows * (D / 4); ch += NT) {
+        const int rl = ch / (D / 4), e0 = ch % (D / 4) * 4;
+        const uint2* src = reinterpret_cast<const uint2*>(sout + rl * LDF + e0);
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{src[0].x, src[0].y, src[1].x, src[1].y},
+                                               part, ((g0 * 32 + rl) * D + e0) * 4, 0,
+                                               MERGE ? kAgentScope : 0);
       }
     }
-  }
-  __syncthreads();
-  {
-    constexpr int EPC = 16 / int(sizeof(T));            // elements per 16-byte chunk
-    constexpr int CPR = D / EPC;                         // chunks per row
-    const int nrows = it.nrows;
-    for (int ch = tid; ch < nrows * CPR; ch += NT) {
-      const int rl = ch / CPR, e0 = (ch % CPR) * EPC;
-      const T* src = sbuf + rl * LDO + e0;
-      const uint2 lo = *reinterpret_cast<const uint2*>(src);
-      const uint2 hi = *reinterpret_cast<const uint2*>(src + EPC / 2);
-      if (it.partial < 0) {
-        const int r = it.row0 + rl;
-        T* dst = static_cast<T*>(a.out) + ((size_t(b) * S + r / G) * a.Hq + g * G + r % G) * D + e0;
-        *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      } else {
-        const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
-            static_cast<T*>(a.part_o) + size_t(it.partial) * a.RB * D, 0,
-            a.RB * D * int(sizeof(T)), kBufferFlags);
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo.x, lo.y, hi.x, hi.y}, part,
-                                               (rl * D + e0) * int(sizeof(T)), 0,
-                                               MERGE ? kAgentScope : 0);
+  } else {
+    constexpr int LDO = D + (sizeof(T) == 2 ? 4 : 2);   // staged row, 8-byte aligned
+    static_assert(NRG * 32 * LDO <= SBUF, "staged rows must fit in the tile stages");
+    if constexpr (KG == 2) __syncthreads();   // the key-half exchange is read before reuse
+    if (writer) {
+      T* srow = sbuf + (rgrp * 32 + qi) * LDO;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int d = 32 * db + 8 * i + 4 * half;
+          const float x0 = o[db][4 * i] * inv, x1 = o[db][4 * i + 1] * inv;
+          const float x2 = o[db][4 * i + 2] * inv, x3 = o[db][4 * i + 3] * inv;
+          if constexpr (sizeof(T) == 4) {
+            reinterpret_cast<float2*>(srow + d)[0] = make_float2(x0, x1);
+            reinterpret_cast<float2*>(srow + d)[1] = make_float2(x2, x3);
+          } else {
+            *reinterpret_cast<uint2*>(srow + d) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
+          }
+        }
+      if (row_ok && half == 0) {
+        if (it.partial < 0) {
+          if (a.lse) a.lse[(size_t(b) * a.Hq + h) * S + t] = lse_val;
+        } else {
+          float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
+          if constexpr (MERGE)
+            __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else
+            *dst = lse_val;
+        }
+      }
+    }
+    __syncthreads();
+    {
+      constexpr int EPC = 16 / int(sizeof(T));            // elements per 16-byte chunk
+      constexpr int CPR = D / EPC;                         // chunks per row
+      const int nrows = it.nrows;
+      for (int ch = tid; ch < nrows * CPR; ch += NT) {
+        const int rl = ch / CPR, e0 = (ch % CPR) * EPC;
+        const T* src = sbuf + rl * LDO + e0;
+        const uint2 lo = *reinterpret_cast<const uint2*>(src);
+        const uint2 hi = *reinterpret_cast<const uint2*>(src + EPC / 2);
+        if (it.partial < 0) {
+          const int r = it.row0 + rl;
+          T* dst =
+              static_cast<T*>(a.out) + ((size_t(b) * S + r / G) * a.Hq + g * G + r % G) * D + e0;
+          *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        } else {
+          const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
+              static_cast<T*>(a.part_o) + size_t(it.partial) * a.RB * D, 0,
+              a.RB * D * int(sizeof(T)), kBufferFlags);
+          typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+          __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo.x, lo.y, hi.x, hi.y}, part,
+                                                 (rl * D + e0) * int(sizeof(T)), 0,
+                                                 MERGE ? kAgentScope : 0);
+        }
       }
     }
   }
@@ -1490,7 +1541,7 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       s_last = atomicInc(a.counters + it.merge, last) == last;
     }
     __syncthreads();
-    if (s_last) merge_splits<T, D, NT>(mg, a, reinterpret_cast<float*>(sbuf), tid);
+    if (s_last) merge_splits<T, PT, D, NT>(mg, a, reinterpret_cast<float*>(sbuf), tid);
   }
 }
 
@@ -1506,14 +1557,14 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 // splits each take one more.  Partial rows are loaded only for the group's own
 // splits (a branch uniform over the workgroup): clamped duplicates to fill a
 // batch of 32 cost more than a second round trip.
-template <typename T, int D>
+template <typename T, typename PT, int D>
 __global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
   constexpr int EPT = 4;
   constexpr int TPR = D / EPT;                 // threads per row
   constexpr int RPW = 256 / TPR;               // rows per workgroup
   constexpr int NPS = kMaxSplits / TPR;        // split LSEs per thread
   constexpr int NB = 32;                       // splits per batch of partial-row loads
-  constexpr int WPE = EPT * sizeof(T) / 4;     // 32-bit words of a thread's elements
+  constexpr int WPE = EPT * sizeof(PT) / 4;    // 32-bit words of a thread's elements
   __shared__ float s_w[kMaxSplits][RPW];
   const MergeGroup mg = a.groups[blockIdx.x];
   const int rlo = blockIdx.y * RPW;
@@ -1530,7 +1581,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
   float li[NPS];
 #pragma unroll
   for (int k = 0; k < NPS; ++k) li[k] = pl[size_t(min(sub + k * TPR, last)) * a.RB];
-  const T* po = static_cast<const T*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
+  const PT* po =
+      static_cast<const PT*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
   uint32_t w[NB][WPE];                         // raw partial elements, decoded at use
   auto load_batch = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
@@ -1612,13 +1664,13 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
 // up to SPL * SPB splits take one memory round trip; the maximum, the sum of
 // weights and the weighted rows are reduced across lanes through LDS.  Later
 // batches of SPB splits per lane each take one more.
-template <typename T, int D>
+template <typename T, typename PT, int D>
 __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
   constexpr int EPT = 4;
   constexpr int TPR = D / EPT;                 // threads per row
   constexpr int SPL = 256 / TPR;               // split lanes
   constexpr int SPB = 8;                       // splits per lane per batch
-  constexpr int WPE = EPT * sizeof(T) / 4;     // 32-bit words of a thread's elements
+  constexpr int WPE = EPT * sizeof(PT) / 4;    // 32-bit words of a thread's elements
   __shared__ float s_red[256];
   __shared__ float s_acc[SPL][D];
   const MergeGroup mg = a.groups[blockIdx.x];
@@ -1627,7 +1679,8 @@ __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
   const int tid = threadIdx.x, sl = tid / TPR, sub = tid % TPR;
   const int last = mg.nsplit - 1;
   const float* pl = a.part_lse + size_t(mg.part0) * a.RB + rloc;
-  const T* po = static_cast<const T*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
+  const PT* po =
+      static_cast<const PT*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
 
   // a batch: splits i0 + k * SPL, k < SPB, from indices clamped to the last
   // split (unconditional loads; what lies past it gets weight zero)
@@ -1899,31 +1952,53 @@ T* at_mut(void* base, size_t off) {
   return reinterpret_cast<T*>(static_cast<uint8_t*>(base) + off);
 }
 
-template <typename T, int D, int SRC>
+template <typename T, typename PT, int D, int SRC, int KG, int NT>
+const void* attn_of(bool merge) {
+  return merge ? reinterpret_cast<const void*>(&attn_kernel<T, PT, D, SRC, KG, NT, true>)
+               : reinterpret_cast<const void*>(&attn_kernel<T, PT, D, SRC, KG, NT, false>);
+}
+
+template <typename T, typename PT, int D, int SRC>
 hipError_t launch_attn_t(const Plan& p, const AttnParams& ap, hipStream_t st, hipEvent_t e0,
                          hipEvent_t e1) {
   const dim3 grid(static_cast<unsigned>(p.items.size()));
   const bool merge = p.merge_in_kernel;
-  if (p.rows_per_block == 64) {
-    const void* k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, true>)
-                          : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 256, false>);
-    return launch(k, grid, dim3(256), st, ap, e0, e1);
-  }
-  const void* k;
-  if (p.rows_per_block == 256)
-    k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 1, 512, true>)
-              : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 1, 512, false>);
-  else
-    k = merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 512, true>)
-              : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, 2, 512, false>);
-  return launch(k, grid, dim3(512), st, ap, e0, e1);
+  if (p.rows_per_block == 64)
+    return launch(attn_of<T, PT, D, SRC, 2, 256>(merge), grid, dim3(256), st, ap, e0, e1);
+  return launch(p.rows_per_block == 256 ? attn_of<T, PT, D, SRC, 1, 512>(merge)
+                                        : attn_of<T, PT, D, SRC, 2, 512>(merge),
+                grid, dim3(512), st, ap, e0, e1);
 }
 
 template <typename T, int SRC>
 hipError_t launch_attn_d(const Plan& p, const AttnParams& ap, hipStream_t st, hipEvent_t e0,
                          hipEvent_t e1) {
-  return p.cfg.head_dim == 64 ? launch_attn_t<T, 64, SRC>(p, ap, st, e0, e1)
-                              : launch_attn_t<T, 128, SRC>(p, ap, st, e0, e1);
+  const int D = p.cfg.head_dim;
+  if constexpr (sizeof(T) == 2 && SRC != SRC_PAGED_SIF) {
+    if (p.part_f32)
+      return D == 64 ? launch_attn_t<T, float, 64, SRC>(p, ap, st, e0, e1)
+                     : launch_attn_t<T, float, 128, SRC>(p, ap, st, e0, e1);
+  }
+  return D == 64 ? launch_attn_t<T, T, 64, SRC>(p, ap, st, e0, e1)
+                 : launch_attn_t<T, T, 128, SRC>(p, ap, st, e0, e1);
+}
+
+template <typename T, typename PT>
+hipError_t launch_merge_t(const Plan& p, const MergeParams& mp, hipStream_t st, hipEvent_t e0,
+                          hipEvent_t e1) {
+  const int D = p.cfg.head_dim;
+  const unsigned n = static_cast<unsigned>(p.merges.size());
+  if (p.max_splits > kSplitMergeMin && p.rows_per_block <= 128) {
+    // many splits over few rows: one workgroup per row, splits spread over lanes
+    // (256-row blocks have rows enough to fill the machine with 8 rows a group)
+    return launch(D == 64 ? reinterpret_cast<const void*>(&merge_split_kernel<T, PT, 64>)
+                          : reinterpret_cast<const void*>(&merge_split_kernel<T, PT, 128>),
+                  dim3(n, p.rows_per_block), dim3(256), st, mp, e0, e1);
+  }
+  const int rpw = 256 / (D / 4);
+  return launch(D == 64 ? reinterpret_cast<const void*>(&merge_kernel<T, PT, 64>)
+                        : reinterpret_cast<const void*>(&merge_kernel<T, PT, 128>),
+                dim3(n, (p.rows_per_block + rpw - 1) / rpw), dim3(256), st, mp, e0, e1);
 }
 
 }  // namespace
@@ -1994,30 +2069,9 @@ hipError_t launch_merge(const Plan& p, void* ws, void* out, float* lse, hipStrea
   mp.part_lse = at<float>(ws, p.ws.part_lse);
   mp.out = out;
   mp.lse = lse;
-  const int D = p.cfg.head_dim;
-  if (p.max_splits > kSplitMergeMin && p.rows_per_block <= 128) {
-    // many splits over few rows: one workgroup per row, splits spread over lanes
-    // (256-row blocks have rows enough to fill the machine with 8 rows a group)
-    const dim3 grid(static_cast<unsigned>(p.merges.size()), p.rows_per_block);
-    const void* k;
-    if (p.cfg.act_dtype == C2KV_F32)
-      k = D == 64 ? reinterpret_cast<const void*>(&merge_split_kernel<float, 64>)
-                  : reinterpret_cast<const void*>(&merge_split_kernel<float, 128>);
-    else
-      k = D == 64 ? reinterpret_cast<const void*>(&merge_split_kernel<__bf16, 64>)
-                  : reinterpret_cast<const void*>(&merge_split_kernel<__bf16, 128>);
-    return launch(k, grid, dim3(256), st, mp, e0, e1);
-  }
-  const int rpw = 256 / (D / 4);
-  const dim3 grid(static_cast<unsigned>(p.merges.size()), (p.rows_per_block + rpw - 1) / rpw);
-  const void* k;
-  if (p.cfg.act_dtype == C2KV_F32)
-    k = D == 64 ? reinterpret_cast<const void*>(&merge_kernel<float, 64>)
-                : reinterpret_cast<const void*>(&merge_kernel<float, 128>);
-  else
-    k = D == 64 ? reinterpret_cast<const void*>(&merge_kernel<__bf16, 64>)
-                : reinterpret_cast<const void*>(&merge_kernel<__bf16, 128>);
-  return launch(k, grid, dim3(256), st, mp, e0, e1);
+  if (p.cfg.act_dtype == C2KV_F32) return launch_merge_t<float, float>(p, mp, st, e0, e1);
+  if (p.part_f32) return launch_merge_t<__bf16, float>(p, mp, st, e0, e1);
+  return launch_merge_t<__bf16, __bf16>(p, mp, st, e0, e1);
 }
 
 hipError_t launch_compose(const Plan& p, void* ws, int pool_dtype, const void* k, const void* v,

@@ -63,6 +63,7 @@ struct Work {
   std::vector<std::vector<WorkItem>> queue{kXcds};
   std::vector<MergeGroup> merges;
   int32_t n_partials = 0, max_splits = 1;
+  int32_t part_bytes = 4;         // of a partial's element
 
   // merge group of a row block with `ns` splits (-1 where it has one)
   int32_t add_merge(int32_t b, int32_t g, int32_t row0, int32_t nrows, int32_t ns) {
@@ -397,8 +398,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     w.merges = take(sizeof(MergeGroup) * wk.merges.size());
     w.counters = take(sizeof(int32_t) * wk.merges.size());
     w.table_bytes = off;
-    const size_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
-    w.part_o = take(act_bytes * size_t(wk.n_partials) * RB * D);
+    w.part_o = take(size_t(wk.part_bytes) * wk.n_partials * RB * D);
     w.part_lse = take(sizeof(float) * size_t(wk.n_partials) * RB);
     w.total = off;
     return w;
@@ -415,7 +415,9 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
                     p.req_slot0[gr.b], p.req_slot0[gr.b + 1] - p.req_slot0[gr.b],
                     p.block_table[size_t(gr.b) * p.max_pages], 0, {0, 0, 0}, 0};
   };
+  const int32_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
   Work even_splits;
+  even_splits.part_bytes = act_bytes;
   for (const Group& gr : groups) {
     Work& wk = even_splits;
     // a SIF row block over several key ranges is one item that runs through
@@ -556,9 +558,31 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     if (!wk.merges.empty())
       worst += kMergeTiles;
     for (const MergeGroup& m : wk.merges)
-      worst += double(m.nsplit) * m.nrows * cfg.head_dim *
-               (cfg.act_dtype == C2KV_F32 ? 4 : 2) / kTileBytes;
+      worst += double(m.nsplit) * m.nrows * cfg.head_dim * wk.part_bytes / kTileBytes;
     return worst;
+  };
+  // Rounding of 16-bit partials, by row block: the squares of its splits' shares of the
+  // tiles (each split is rounded on its own), 0 where it is whole.
+  auto rounding = [&](const Work& wk) {
+    std::vector<double> var(groups.size(), 0.0);
+    for (const WorkItem& w : wk.items) {
+      if (w.merge < 0) continue;
+      const size_t i = (size_t(w.b) * cfg.n_kv_heads + w.g) * n_rb + w.row0 / RB;
+      const double share = double(w.tile1 - w.tile0) / groups[i].tiles;
+      var[i] += share * share;
+    }
+    return var;
+  };
+  // `cut` in 16 bits rounds no more than `even`: no row block that is whole there, and no
+  // more in all
+  auto rounds_no_more = [&](const Work& cut, const Work& even) {
+    const std::vector<double> c = rounding(cut), e = rounding(even);
+    double more = 0;
+    for (size_t i = 0; i < groups.size(); ++i) {
+      if (c[i] > 0 && e[i] == 0) return false;
+      more += groups[i].nrows * (c[i] - e[i]);
+    }
+    return more <= 0;
   };
   even_splits.order();
   Work* work = &even_splits;
@@ -566,13 +590,22 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // Even splits that fit one round of slots are balanced to the rounding of a tile: only
   // lists of more items are cut (24 fp32 row blocks of 256 rows, 4 to 16 tiles each, ran
   // 60 us in pieces of one and two tiles and 99 us cut into pieces of up to four).
+  // Their pieces are held in fp32, as the accumulators of a whole row block are (in bf16 the
+  // error against 64 bits of 288 row blocks that were whole, 18 requests of 174 tokens, was
+  // 0.0052; whole and in fp32 it is 0.0050).  Where that does not fit the static scratch
+  // that the even splits fit, 16 bits serve if they round no more than the even splits' do
+  // (int8 ragged batch of 3: 0.00569 in both lists); else the even splits stay.
   if (!sif && o.kv_splits == 0 && int64_t(even_splits.items.size()) > target) {
+    auto fits = [&](const Work& wk) { return layout(wk).total <= C2KV_STATIC_SCRATCH_BYTES; };
     by_slot = cut_by_slot();
     by_slot.order();
-    if (makespan(by_slot) < kCutGain * makespan(even_splits) &&
-        (layout(by_slot).total <= C2KV_STATIC_SCRATCH_BYTES ||
-         layout(even_splits).total > C2KV_STATIC_SCRATCH_BYTES))
-      work = &by_slot;
+    by_slot.part_bytes = 4;
+    bool allowed = fits(by_slot) || !fits(even_splits);
+    if (!allowed && act_bytes == 2) {
+      by_slot.part_bytes = 2;
+      allowed = fits(by_slot) && rounds_no_more(by_slot, even_splits);
+    }
+    if (allowed && makespan(by_slot) < kCutGain * makespan(even_splits)) work = &by_slot;
   }
   // The last split of a row block to finish merges it where that takes one workgroup
   // little (few splits), and either other workgroups run meanwhile (more than one
@@ -584,8 +617,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // 64 rows in 5 splits, one round, 28.0 -> 29.2, 18 splits of 256 rows 16.0 -> 33.3.
   int64_t merge_bytes = 0;
   for (const MergeGroup& m : work->merges)
-    merge_bytes = std::max(merge_bytes, int64_t(m.nsplit) * m.nrows * D *
-                                            (cfg.act_dtype == C2KV_F32 ? 4 : 2));
+    merge_bytes = std::max(merge_bytes, int64_t(m.nsplit) * m.nrows * D * work->part_bytes);
   p.merge_in_kernel =
       o.merge_mode == 1 ||
       (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
@@ -596,6 +628,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   p.merges = std::move(work->merges);
   p.n_partials = work->n_partials;
   p.max_splits = work->max_splits;
+  p.part_f32 = work->part_bytes == 4;
 
   // ---- workspace image --------------------------------------------------------
   const WorkspaceLayout& w = p.ws;

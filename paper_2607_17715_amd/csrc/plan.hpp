@@ -49,7 +49,7 @@ struct WorkspaceLayout {
   size_t merges = 0;      // MergeGroup [n_merge]
   size_t counters = 0;    // int32 [n_merge], zero between launches
   size_t table_bytes = 0; // end of the tables (uploaded image size)
-  size_t part_o = 0;      // activation dtype [n_partials][rows_per_block][D]
+  size_t part_o = 0;      // activation dtype (fp32 if part_f32) [n_partials][rows_per_block][D]
   size_t part_lse = 0;    // float [n_partials][rows_per_block]
   size_t total = 0;
 };
@@ -85,6 +85,7 @@ struct Plan {
   std::vector<WorkItem> items;
   std::vector<MergeGroup> merges;
   int32_t n_partials = 0, max_splits = 1;
+  bool part_f32 = false;          // partials in fp32 whatever the activation dtype
   bool merge_in_kernel = false;   // last split of a row block merges (else a merge kernel)
 
   // tables in float (host image)

@@ -1,12 +1,14 @@
 """Row blocks cut where a workgroup slot is full: splits of unequal length.
 
 CPU: tests/work_split.cpp checks that the work lists of random ragged batches cover
-every key tile of every row block exactly once.  GPU: few compute units are declared, so
-that small batches are cut this way, for row blocks of each size and each key source."""
+every key tile of every row block exactly once, and that no row block that equal splits
+would leave whole gets 16-bit partials.  GPU: few compute units are declared, so that small
+batches are cut this way, for row blocks of each size and each key source."""
 import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 import torch  # noqa: F401  (before the library, so that both share one HIP runtime)
 
@@ -63,3 +65,25 @@ def test_cut_row_blocks_parity(shape, num_cus):
     groups = w.batch * w.n_kv_heads * -(-w.suffix_len * (w.n_q_heads // w.n_kv_heads) //
                                         i["rows_per_block"])
     assert i["n_merge_groups"] > 0 and i["n_work_items"] % groups != 0, (groups, i)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,num_cus", CASES[:3])
+def test_cut_row_blocks_round_once(shape, num_cus):
+    """Row blocks that equal splits would leave whole (at least one per slot) are rounded
+    to bf16 once, as they are when whole.  With q = 0 every probability is exactly 1, so
+    that an output is the mean of values drawn from [1, 2) and nothing but its own
+    rounding, half a unit of 2^-7, and fp32 sums (relative 2^-24 for each of about 100
+    steps, and the weights' 1e-6: 1e-5 of values below 2) separate it from float64."""
+    from gpu_common import oracle_ref, run_fused, run_paged
+    w = synth.small(seed=33, keep=("ratio", 0.4, 0.9), **dict(shape, pool_dtype="bf16"))
+    rng = np.random.default_rng(7)
+    values = lambda a: synth.cast_f64(1 + rng.integers(0, 128, a.shape) / 128, "bf16")
+    w = synth.with_overrides(w, q=np.zeros_like(w.q), pool_v=values(w.pool_v),
+                             v_suf=values(w.v_suf))
+    ref, _, _ = oracle_ref(w)
+    out, _, plan, dev = run_fused(w, num_cus=num_cus)
+    assert plan.info["n_merge_groups"] > 0
+    paged, _, _, _, _ = run_paged(w, dev=dev, plan=plan)
+    assert torch.equal(out, paged)
+    assert np.abs(c2kv.to_numpy_f64(out) - ref).max() <= 2.0 ** -8 + 2e-5

@@ -1,8 +1,9 @@
 // Checks the attention work list of ragged batches (plan.cpp, host code only):
 // the items of every row block cover its key tiles exactly once, in order, each
 // split with a partial of its own inside its merge group.
-// Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n>" (cut: plans with
-// row blocks split in unequal numbers of pieces, though no count was asked for).
+// Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n> whole <m>" (cut: plans
+// with row blocks split in unequal numbers of pieces, though no count was asked for; whole:
+// cut plans whose row blocks equal splits would all leave whole).
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -18,7 +19,7 @@ int main(int argc, char** argv) {
   const int iters = argc > 1 ? atoi(argv[1]) : 300;
   std::mt19937_64 rng(argc > 2 ? atoll(argv[2]) : 1);
   auto U = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
-  int cut = 0;
+  int cut = 0, whole = 0;
   for (int it = 0; it < iters; ++it) {
     c2kv_attn_cfg cfg{};
     const int hk[] = {1, 2, 4, 8}, G[] = {1, 3, 4, 8};
@@ -76,9 +77,15 @@ int main(int argc, char** argv) {
       }
     }
     CHECK(int(partials.size()) == p.n_partials);
+    // with at least one row block per slot, equal splits leave all of them whole
+    const int cu = o.num_cus > 0 ? o.num_cus : 256;
+    if (int(blocks.size()) >= cu * (RB == 64 ? 2 : 1) && !p.merges.empty()) {
+      CHECK(p.part_f32);
+      ++whole;
+    }
     CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * RB <= p.ws.total);
     if (sizes.size() > 1 && *sizes.rbegin() <= 8) ++cut;
   }
-  std::printf("ok %d cut %d\n", iters, cut);
+  std::printf("ok %d cut %d whole %d\n", iters, cut, whole);
   return 0;
 }
