@@ -235,7 +235,8 @@ __device__ inline uint4 keep_first(uint4 v, int n_keep) {
 // ----------------------------------------------------------------------------
 
 struct AttnParams {
-  int Hq, Hkv, G, S, PS, max_pages, RB, n_seg;
+  int Hq, Hkv, G, S, PS, max_pages, n_seg;
+  int PR;                       // rows of a partial
   int sif_n, sif_block, sif_sink;  // SIF mask over the suffix when sif_n > 0
   int tpp;                      // key tiles per page (PS / KT)
   unsigned tpp_magic;           // floor(2^32 / tpp) + 1 (tpp > 1)
@@ -257,7 +258,7 @@ struct AttnParams {
   const void* v_suf;
   void* out;
   float* lse;
-  void* part_o;                 // [n_partials][RB][D], activation dtype
+  void* part_o;                 // [n_partials][PR][D] (an fp32 one beside bf16 takes two)
   float* part_lse;
 };
 
@@ -278,7 +279,7 @@ struct ComposeParams {
 };
 
 struct MergeParams {
-  int Hq, G, S, RB;
+  int Hq, G, S, PR;
   const MergeGroup* groups;
   const void* part_o;
   const float* part_lse;
@@ -382,10 +383,11 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
   constexpr int EPT = 16 / int(sizeof(PT));     // elements per chunk
   constexpr int CPR = D / EPT;                  // chunks per row
   const int units = mg.nrows * CPR, ns = mg.nsplit;
-  const float* pl = a.part_lse + size_t(mg.part0) * a.RB;
+  constexpr int US = sizeof(PT) / sizeof(T);    // partials a split takes
+  const float* pl = a.part_lse + size_t(mg.part0) * a.PR;
   const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(
-      static_cast<PT*>(a.part_o) + size_t(mg.part0) * a.RB * D, 0,
-      ns * a.RB * D * int(sizeof(PT)), kBufferFlags);
+      static_cast<T*>(a.part_o) + size_t(mg.part0) * a.PR * D, 0,
+      ns * a.PR * D * int(sizeof(PT)), kBufferFlags);
   auto store_row = [&](int u, float mx, float z, const float (&acc)[EPT])
       __attribute__((always_inline)) {
     const int rloc = u / CPR, e0 = (u % CPR) * EPT;
@@ -430,9 +432,9 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           const int sp = min(i + j * istep, ns - 1);
-          l[k][j] = load_shared(pl + size_t(sp) * a.RB + rloc);
+          l[k][j] = load_shared(pl + size_t(sp * US) * a.PR + rloc);
           const auto x = __builtin_amdgcn_raw_buffer_load_b128(
-              po, ((sp * a.RB + rloc) * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
+              po, ((sp * a.PR + rloc) * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
           w[k][j][0] = x[0]; w[k][j][1] = x[1]; w[k][j][2] = x[2]; w[k][j][3] = x[3];
         }
       }
@@ -879,8 +881,8 @@ struct TileLoader {
 // to a CU, so that two work items' latencies overlap.  MERGE: the last split of a row
 // block merges it where the plan says so (kernels of their own: the merge raises the
 // registers of some, and SIF extraction measured 1.1 % slower with it behind a branch).
-// PT: type of the partials (float where the plan holds them so: Plan::part_f32).
-template <typename T, typename PT, int D, int SRC, int KG, int NT, bool MERGE>
+// P32: some row blocks' partials are fp32 beside bf16 tiles (WorkItem::part_f32).
+template <typename T, int D, int SRC, int KG, int NT, bool MERGE, bool P32>
 __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   constexpr int NRG = NT / 64 / KG;         // row groups
   constexpr int NKB = 2 / KG;               // 32-key blocks per wavefront and tile
@@ -1420,23 +1422,23 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 
   // ---- epilogue: rows normalised and staged in LDS (accumulator value v of
   // block db holds d = 32*db + 8*(v/4) + 4*half + v%4), then copied out as
-  // whole rows: to the output, or as PT to the partials
+  // whole rows: to the output, or to the partials in the activation dtype or in fp32
   const float l_tot = half_pair_sum(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   const float lse_val = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
-  if (!std::is_same<T, PT>::value && it.partial >= 0) {
+  if (P32 && it.part_f32) {
     // fp32 partials beside bf16 tiles, in passes of as many row groups as both tile stages
     // hold (256 rows take two)
     constexpr int LDF = D + 2;                           // staged row, 8-byte aligned
     constexpr int GPP = NRG * 32 * LDF * 4 <= SBUF * int(sizeof(T)) ? NRG : NRG / 2;
-    static_assert(sizeof(T) == sizeof(PT) || GPP * 32 * LDF * 4 <= SBUF * int(sizeof(T)),
+    static_assert(!P32 || GPP * 32 * LDF * 4 <= SBUF * int(sizeof(T)),
                   "staged rows must fit in the tile stages");
     float* const sout = reinterpret_cast<float*>(sbuf);
     const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
-        static_cast<float*>(a.part_o) + size_t(it.partial) * a.RB * D, 0, a.RB * D * 4,
+        static_cast<T*>(a.part_o) + size_t(it.partial) * a.PR * D, 0, a.PR * D * 4,
         kBufferFlags);
     if (writer && row_ok && half == 0) {
-      float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
+      float* dst = a.part_lse + size_t(it.partial) * a.PR + rloc;
       if constexpr (MERGE)
         __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       else
@@ -1492,7 +1494,7 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
         if (it.partial < 0) {
           if (a.lse) a.lse[(size_t(b) * a.Hq + h) * S + t] = lse_val;
         } else {
-          float* dst = a.part_lse + size_t(it.partial) * a.RB + rloc;
+          float* dst = a.part_lse + size_t(it.partial) * a.PR + rloc;
           if constexpr (MERGE)
             __hip_atomic_store(dst, lse_val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           else
@@ -1517,8 +1519,8 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
           *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         } else {
           const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(
-              static_cast<T*>(a.part_o) + size_t(it.partial) * a.RB * D, 0,
-              a.RB * D * int(sizeof(T)), kBufferFlags);
+              static_cast<T*>(a.part_o) + size_t(it.partial) * a.PR * D, 0,
+              a.PR * D * int(sizeof(T)), kBufferFlags);
           typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
           __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo.x, lo.y, hi.x, hi.y}, part,
                                                  (rl * D + e0) * int(sizeof(T)), 0,
@@ -1541,7 +1543,11 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
       s_last = atomicInc(a.counters + it.merge, last) == last;
     }
     __syncthreads();
-    if (s_last) merge_splits<T, PT, D, NT>(mg, a, reinterpret_cast<float*>(sbuf), tid);
+    if (s_last) {
+      float* const xs = reinterpret_cast<float*>(sbuf);
+      if (P32 && mg.f32) merge_splits<T, float, D, NT>(mg, a, xs, tid);
+      else merge_splits<T, T, D, NT>(mg, a, xs, tid);
+    }
   }
 }
 
@@ -1558,38 +1564,38 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
 // splits (a branch uniform over the workgroup): clamped duplicates to fill a
 // batch of 32 cost more than a second round trip.
 template <typename T, typename PT, int D>
-__global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
+__device__ __forceinline__ void merge_block(const MergeParams& a, const MergeGroup& mg, float* sw) {
   constexpr int EPT = 4;
   constexpr int TPR = D / EPT;                 // threads per row
   constexpr int RPW = 256 / TPR;               // rows per workgroup
+  constexpr int US = sizeof(PT) / sizeof(T);   // partials a split takes
   constexpr int NPS = kMaxSplits / TPR;        // split LSEs per thread
   constexpr int NB = 32;                       // splits per batch of partial-row loads
   constexpr int WPE = EPT * sizeof(PT) / 4;    // 32-bit words of a thread's elements
-  __shared__ float s_w[kMaxSplits][RPW];
-  const MergeGroup mg = a.groups[blockIdx.x];
+  float(*s_w)[RPW] = reinterpret_cast<float(*)[RPW]>(sw);    // [kMaxSplits]
   const int rlo = blockIdx.y * RPW;
   if (rlo >= mg.nrows) return;
   const int tid = threadIdx.x, rl = tid / TPR, sub = tid % TPR;
   const int rloc = rlo + rl;
   const bool ok = rloc < mg.nrows;
-  const float* pl = a.part_lse + size_t(mg.part0) * a.RB + rloc;
+  const float* pl = a.part_lse + size_t(mg.part0) * a.PR + rloc;
 
   // LSE loads are unconditional, from indices clamped into the group's partials
-  // (rows of a partial exist up to RB); what lies past the row count or the
+  // (rows of a partial exist up to PR, a multiple of 16); what lies past the row count or the
   // split count gets weight zero.
   const int last = mg.nsplit - 1;
   float li[NPS];
 #pragma unroll
-  for (int k = 0; k < NPS; ++k) li[k] = pl[size_t(min(sub + k * TPR, last)) * a.RB];
-  const PT* po =
-      static_cast<const PT*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
+  for (int k = 0; k < NPS; ++k) li[k] = pl[size_t(min(sub + k * TPR, last) * US) * a.PR];
+  const PT* po = static_cast<const PT*>(a.part_o) +
+                 (size_t(mg.part0) * a.PR / US + rloc) * D + sub * EPT;
   uint32_t w[NB][WPE];                         // raw partial elements, decoded at use
   auto load_batch = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       if (i0 + k > last) break;                // uniform: this group's splits only
       const uint32_t* src =
-          reinterpret_cast<const uint32_t*>(po + size_t(i0 + k) * a.RB * D);
+          reinterpret_cast<const uint32_t*>(po + size_t(i0 + k) * a.PR * D);
       if constexpr (WPE == 4) {
         const uint4 x = *reinterpret_cast<const uint4*>(src);
         w[k][0] = x.x; w[k][1] = x.y; w[k][2] = x.z; w[k][3] = x.w;
@@ -1658,6 +1664,15 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
     a.lse[(size_t(mg.b) * a.Hq + h) * a.S + t] = z > 0.f ? mx + __logf(z) : kNegInf;
 }
 
+// (P32: some row blocks' partials are fp32 beside bf16 outputs)
+template <typename T, int D, bool P32>
+__global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
+  __shared__ float s_w[kMaxSplits * (256 / (D / 4))];
+  const MergeGroup mg = a.groups[blockIdx.x];
+  if (P32 && mg.f32) merge_block<T, float, D>(a, mg, s_w);
+  else merge_block<T, T, D>(a, mg, s_w);
+}
+
 // One row per workgroup, the splits spread over SPL split lanes of TPR threads
 // (row blocks with few rows and many splits: decode, short suffixes).  Each
 // thread loads its first SPB splits' LSEs and partial elements together, so that
@@ -1665,22 +1680,22 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams a) {
 // weights and the weighted rows are reduced across lanes through LDS.  Later
 // batches of SPB splits per lane each take one more.
 template <typename T, typename PT, int D>
-__global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
+__device__ __forceinline__ void merge_row(const MergeParams& a, const MergeGroup& mg, float* s_red,
+                                          float* sa) {
   constexpr int EPT = 4;
   constexpr int TPR = D / EPT;                 // threads per row
   constexpr int SPL = 256 / TPR;               // split lanes
   constexpr int SPB = 8;                       // splits per lane per batch
   constexpr int WPE = EPT * sizeof(PT) / 4;    // 32-bit words of a thread's elements
-  __shared__ float s_red[256];
-  __shared__ float s_acc[SPL][D];
-  const MergeGroup mg = a.groups[blockIdx.x];
+  constexpr int US = sizeof(PT) / sizeof(T);   // partials a split takes
+  float(*s_acc)[D] = reinterpret_cast<float(*)[D]>(sa);      // [SPL]
   const int rloc = blockIdx.y;
   if (rloc >= mg.nrows) return;
   const int tid = threadIdx.x, sl = tid / TPR, sub = tid % TPR;
   const int last = mg.nsplit - 1;
-  const float* pl = a.part_lse + size_t(mg.part0) * a.RB + rloc;
-  const PT* po =
-      static_cast<const PT*>(a.part_o) + (size_t(mg.part0) * a.RB + rloc) * D + sub * EPT;
+  const float* pl = a.part_lse + size_t(mg.part0) * a.PR + rloc;
+  const PT* po = static_cast<const PT*>(a.part_o) +
+                 (size_t(mg.part0) * a.PR / US + rloc) * D + sub * EPT;
 
   // a batch: splits i0 + k * SPL, k < SPB, from indices clamped to the last
   // split (unconditional loads; what lies past it gets weight zero)
@@ -1690,8 +1705,8 @@ __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
 #pragma unroll
     for (int k = 0; k < SPB; ++k) {
       const int i = min(i0 + k * SPL, last);
-      l[k] = pl[size_t(i) * a.RB];
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(po + size_t(i) * a.RB * D);
+      l[k] = pl[size_t(i * US) * a.PR];
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(po + size_t(i) * a.PR * D);
       if constexpr (WPE == 4) {
         const uint4 x = *reinterpret_cast<const uint4*>(src);
         w[k][0] = x.x; w[k][1] = x.y; w[k][2] = x.z; w[k][3] = x.w;
@@ -1711,7 +1726,7 @@ __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
   for (int i0 = sl + SPL * SPB; i0 <= last; i0 += SPL * SPB) {
     float lk[SPB];
 #pragma unroll
-    for (int k = 0; k < SPB; ++k) lk[k] = pl[size_t(min(i0 + k * SPL, last)) * a.RB];
+    for (int k = 0; k < SPB; ++k) lk[k] = pl[size_t(min(i0 + k * SPL, last) * US) * a.PR];
 #pragma unroll
     for (int k = 0; k < SPB; ++k) mx = fmaxf(mx, i0 + k * SPL <= last ? lk[k] : kNegInf);
   }
@@ -1770,6 +1785,15 @@ __global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
   }
   if (a.lse && sub == 0)
     a.lse[(size_t(mg.b) * a.Hq + h) * a.S + t] = zt > 0.f ? mx + __logf(zt) : kNegInf;
+}
+
+template <typename T, int D, bool P32>
+__global__ __launch_bounds__(256) void merge_split_kernel(MergeParams a) {
+  __shared__ float s_red[256];
+  __shared__ float s_acc[(256 / (D / 4)) * D];
+  const MergeGroup mg = a.groups[blockIdx.x];
+  if (P32 && mg.f32) merge_row<T, float, D>(a, mg, s_red, s_acc);
+  else merge_row<T, T, D>(a, mg, s_red, s_acc);
 }
 
 // ----------------------------------------------------------------------------
@@ -1952,21 +1976,21 @@ T* at_mut(void* base, size_t off) {
   return reinterpret_cast<T*>(static_cast<uint8_t*>(base) + off);
 }
 
-template <typename T, typename PT, int D, int SRC, int KG, int NT>
+template <typename T, int D, int SRC, int KG, int NT, bool P32>
 const void* attn_of(bool merge) {
-  return merge ? reinterpret_cast<const void*>(&attn_kernel<T, PT, D, SRC, KG, NT, true>)
-               : reinterpret_cast<const void*>(&attn_kernel<T, PT, D, SRC, KG, NT, false>);
+  return merge ? reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, KG, NT, true, P32>)
+               : reinterpret_cast<const void*>(&attn_kernel<T, D, SRC, KG, NT, false, P32>);
 }
 
-template <typename T, typename PT, int D, int SRC>
+template <typename T, int D, int SRC, bool P32>
 hipError_t launch_attn_t(const Plan& p, const AttnParams& ap, hipStream_t st, hipEvent_t e0,
                          hipEvent_t e1) {
   const dim3 grid(static_cast<unsigned>(p.items.size()));
   const bool merge = p.merge_in_kernel;
   if (p.rows_per_block == 64)
-    return launch(attn_of<T, PT, D, SRC, 2, 256>(merge), grid, dim3(256), st, ap, e0, e1);
-  return launch(p.rows_per_block == 256 ? attn_of<T, PT, D, SRC, 1, 512>(merge)
-                                        : attn_of<T, PT, D, SRC, 2, 512>(merge),
+    return launch(attn_of<T, D, SRC, 2, 256, P32>(merge), grid, dim3(256), st, ap, e0, e1);
+  return launch(p.rows_per_block == 256 ? attn_of<T, D, SRC, 1, 512, P32>(merge)
+                                        : attn_of<T, D, SRC, 2, 512, P32>(merge),
                 grid, dim3(512), st, ap, e0, e1);
 }
 
@@ -1976,14 +2000,14 @@ hipError_t launch_attn_d(const Plan& p, const AttnParams& ap, hipStream_t st, hi
   const int D = p.cfg.head_dim;
   if constexpr (sizeof(T) == 2 && SRC != SRC_PAGED_SIF) {
     if (p.part_f32)
-      return D == 64 ? launch_attn_t<T, float, 64, SRC>(p, ap, st, e0, e1)
-                     : launch_attn_t<T, float, 128, SRC>(p, ap, st, e0, e1);
+      return D == 64 ? launch_attn_t<T, 64, SRC, true>(p, ap, st, e0, e1)
+                     : launch_attn_t<T, 128, SRC, true>(p, ap, st, e0, e1);
   }
-  return D == 64 ? launch_attn_t<T, T, 64, SRC>(p, ap, st, e0, e1)
-                 : launch_attn_t<T, T, 128, SRC>(p, ap, st, e0, e1);
+  return D == 64 ? launch_attn_t<T, 64, SRC, false>(p, ap, st, e0, e1)
+                 : launch_attn_t<T, 128, SRC, false>(p, ap, st, e0, e1);
 }
 
-template <typename T, typename PT>
+template <typename T, bool P32>
 hipError_t launch_merge_t(const Plan& p, const MergeParams& mp, hipStream_t st, hipEvent_t e0,
                           hipEvent_t e1) {
   const int D = p.cfg.head_dim;
@@ -1991,13 +2015,13 @@ hipError_t launch_merge_t(const Plan& p, const MergeParams& mp, hipStream_t st, 
   if (p.max_splits > kSplitMergeMin && p.rows_per_block <= 128) {
     // many splits over few rows: one workgroup per row, splits spread over lanes
     // (256-row blocks have rows enough to fill the machine with 8 rows a group)
-    return launch(D == 64 ? reinterpret_cast<const void*>(&merge_split_kernel<T, PT, 64>)
-                          : reinterpret_cast<const void*>(&merge_split_kernel<T, PT, 128>),
+    return launch(D == 64 ? reinterpret_cast<const void*>(&merge_split_kernel<T, 64, P32>)
+                          : reinterpret_cast<const void*>(&merge_split_kernel<T, 128, P32>),
                   dim3(n, p.rows_per_block), dim3(256), st, mp, e0, e1);
   }
   const int rpw = 256 / (D / 4);
-  return launch(D == 64 ? reinterpret_cast<const void*>(&merge_kernel<T, PT, 64>)
-                        : reinterpret_cast<const void*>(&merge_kernel<T, PT, 128>),
+  return launch(D == 64 ? reinterpret_cast<const void*>(&merge_kernel<T, 64, P32>)
+                        : reinterpret_cast<const void*>(&merge_kernel<T, 128, P32>),
                 dim3(n, (p.rows_per_block + rpw - 1) / rpw), dim3(256), st, mp, e0, e1);
 }
 
@@ -2016,7 +2040,7 @@ hipError_t launch_attention(const Plan& p, void* ws, int src_kind, const void* k
   ap.tpp = p.page_size / KT;
   ap.tpp_magic = ap.tpp > 1 ? unsigned((uint64_t(1) << 32) / uint64_t(ap.tpp)) + 1u : 0u;
   ap.max_pages = p.max_pages;
-  ap.RB = p.rows_per_block;
+  ap.PR = p.part_rows;
   ap.n_seg = p.n_segments;
   ap.sif_n = p.sif_n;
   ap.sif_block = p.sif_block;
@@ -2063,15 +2087,15 @@ hipError_t launch_merge(const Plan& p, void* ws, void* out, float* lse, hipStrea
   mp.Hq = p.cfg.n_q_heads;
   mp.G = p.group;
   mp.S = p.suffix_len;
-  mp.RB = p.rows_per_block;
+  mp.PR = p.part_rows;
   mp.groups = at<MergeGroup>(ws, p.ws.merges);
   mp.part_o = at<unsigned char>(ws, p.ws.part_o);
   mp.part_lse = at<float>(ws, p.ws.part_lse);
   mp.out = out;
   mp.lse = lse;
-  if (p.cfg.act_dtype == C2KV_F32) return launch_merge_t<float, float>(p, mp, st, e0, e1);
-  if (p.part_f32) return launch_merge_t<__bf16, float>(p, mp, st, e0, e1);
-  return launch_merge_t<__bf16, __bf16>(p, mp, st, e0, e1);
+  if (p.cfg.act_dtype == C2KV_F32) return launch_merge_t<float, false>(p, mp, st, e0, e1);
+  if (p.part_f32) return launch_merge_t<__bf16, true>(p, mp, st, e0, e1);
+  return launch_merge_t<__bf16, false>(p, mp, st, e0, e1);
 }
 
 hipError_t launch_compose(const Plan& p, void* ws, int pool_dtype, const void* k, const void* v,

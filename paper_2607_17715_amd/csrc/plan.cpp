@@ -63,7 +63,7 @@ struct Work {
   std::vector<std::vector<WorkItem>> queue{kXcds};
   std::vector<MergeGroup> merges;
   int32_t n_partials = 0, max_splits = 1;
-  int32_t part_bytes = 4;         // of a partial's element
+  int32_t part_rows = 0;          // of a partial
 
   // merge group of a row block with `ns` splits (-1 where it has one)
   int32_t add_merge(int32_t b, int32_t g, int32_t row0, int32_t nrows, int32_t ns) {
@@ -72,6 +72,23 @@ struct Work {
     merges.push_back({b, g, row0, nrows, n_partials, ns, 0, 0});
     n_partials += ns;
     return static_cast<int32_t>(merges.size()) - 1;
+  }
+  // renumbers the partials of queued items, two for each split of a group in fp32
+  void number_partials() {
+    std::vector<int32_t> part0(merges.size());
+    n_partials = 0;
+    for (size_t i = 0; i < merges.size(); ++i) {
+      part0[i] = n_partials;
+      n_partials += merges[i].nsplit << merges[i].f32;
+    }
+    for (auto& q : queue)
+      for (WorkItem& w : q) {
+        if (w.merge < 0) continue;
+        const MergeGroup& m = merges[w.merge];
+        w.partial = part0[w.merge] + ((w.partial - m.part0) << m.f32);
+        w.part_f32 = m.f32;
+      }
+    for (size_t i = 0; i < merges.size(); ++i) merges[i].part0 = part0[i];
   }
   // the grid's order: each XCD's items heaviest first, the XCDs interleaved
   void order() {
@@ -375,6 +392,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   }
   // ---- workspace layout of a work list --------------------------------------------
   const int D = cfg.head_dim, H = D / 2;
+  const int32_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
   const int64_t total = static_cast<int64_t>(p.slot_src.size());
   // one cos/sin row per segment (angle delta * theta_i), or per slot for keys
   // stored before RoPE (angle p_new * theta_i); slot_info's second field is the row
@@ -398,10 +416,15 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     w.merges = take(sizeof(MergeGroup) * wk.merges.size());
     w.counters = take(sizeof(int32_t) * wk.merges.size());
     w.table_bytes = off;
-    w.part_o = take(size_t(wk.part_bytes) * wk.n_partials * RB * D);
-    w.part_lse = take(sizeof(float) * size_t(wk.n_partials) * RB);
+    w.part_o = take(size_t(act_bytes) * wk.n_partials * wk.part_rows * D);
+    w.part_lse = take(sizeof(float) * size_t(wk.n_partials) * wk.part_rows);
     w.total = off;
     return w;
+  };
+
+  // row block of an item or merge group
+  auto block_of = [&](const auto& x) {
+    return (size_t(x.b) * cfg.n_kv_heads + x.g) * n_rb + x.row0 / RB;
   };
 
   // Key splits only add parallelism where the row blocks alone leave CUs idle;
@@ -415,9 +438,8 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
                     p.req_slot0[gr.b], p.req_slot0[gr.b + 1] - p.req_slot0[gr.b],
                     p.block_table[size_t(gr.b) * p.max_pages], 0, {0, 0, 0}, 0};
   };
-  const int32_t act_bytes = cfg.act_dtype == C2KV_F32 ? 4 : 2;
   Work even_splits;
-  even_splits.part_bytes = act_bytes;
+  even_splits.part_rows = RB;
   for (const Group& gr : groups) {
     Work& wk = even_splits;
     // a SIF row block over several key ranges is one item that runs through
@@ -540,6 +562,9 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     }
     return wk;
   };
+  auto merge_bytes = [&](const MergeGroup& m) {      // of its partials
+    return int64_t(m.nsplit) * m.nrows * D * (act_bytes << m.f32);
+  };
   // Time of a work list in bf16 key tiles: each XCD's slots taken in the grid's order, and
   // the merge (its launch, and its partials written and read).
   auto makespan = [&](const Work& wk) {
@@ -558,31 +583,52 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     if (!wk.merges.empty())
       worst += kMergeTiles;
     for (const MergeGroup& m : wk.merges)
-      worst += double(m.nsplit) * m.nrows * cfg.head_dim * wk.part_bytes / kTileBytes;
+      worst += double(merge_bytes(m)) / kTileBytes;
     return worst;
   };
-  // Rounding of 16-bit partials, by row block: the squares of its splits' shares of the
-  // tiles (each split is rounded on its own), 0 where it is whole.
-  auto rounding = [&](const Work& wk) {
-    std::vector<double> var(groups.size(), 0.0);
-    for (const WorkItem& w : wk.items) {
-      if (w.merge < 0) continue;
-      const size_t i = (size_t(w.b) * cfg.n_kv_heads + w.g) * n_rb + w.row0 / RB;
-      const double share = double(w.tile1 - w.tile0) / groups[i].tiles;
-      var[i] += share * share;
+  // The pieces of a cut list are held in fp32, as the accumulators of a whole row block are
+  // (in bf16 the error against 64 bits of 288 row blocks that were whole, 18 requests of 174
+  // tokens, was 0.0052; whole, and in fp32, it is 0.0050).  Where that does not fit the
+  // static scratch that the even splits fit, some row blocks stay in bf16: those of most
+  // splits, whose rounding is least, and none that the even splits leave whole.  False where
+  // bf16 then rounds more than the even splits do, by the squares of the splits' shares of
+  // the tiles (each split is rounded on its own).
+  auto widen_partials = [&](Work& cut, const Work& even) {
+    auto rounding = [&](const Work& wk) {
+      std::vector<double> var(groups.size(), 0.0);
+      for (const WorkItem& w : wk.items) {
+        if (w.merge < 0) continue;
+        const size_t i = block_of(w);
+        const double share = double(w.tile1 - w.tile0) / groups[i].tiles;
+        var[i] += groups[i].nrows * share * share;
+      }
+      return var;
+    };
+    const std::vector<double> was = rounding(even);
+    std::vector<double> is = rounding(cut);
+    int64_t spare = std::numeric_limits<int64_t>::max();
+    if (layout(even).total <= C2KV_STATIC_SCRATCH_BYTES)
+      spare = (int64_t(C2KV_STATIC_SCRATCH_BYTES) - 512 - int64_t(layout(cut).total)) /
+              (int64_t(cut.part_rows) * (act_bytes * D + 4));
+    std::vector<MergeGroup*> order;
+    for (MergeGroup& m : cut.merges) order.push_back(&m);
+    std::stable_sort(order.begin(), order.end(), [&](const MergeGroup* x, const MergeGroup* y) {
+      const bool xw = was[block_of(*x)] == 0, yw = was[block_of(*y)] == 0;
+      return xw != yw ? xw : x->nsplit < y->nsplit;
+    });
+    for (MergeGroup* m : order) {
+      if (m->nsplit > spare) {
+        if (was[block_of(*m)] == 0) return false;
+        break;
+      }
+      m->f32 = 1;
+      spare -= m->nsplit;
+      is[block_of(*m)] = 0;
     }
-    return var;
-  };
-  // `cut` in 16 bits rounds no more than `even`: no row block that is whole there, and no
-  // more in all
-  auto rounds_no_more = [&](const Work& cut, const Work& even) {
-    const std::vector<double> c = rounding(cut), e = rounding(even);
+    cut.number_partials();
     double more = 0;
-    for (size_t i = 0; i < groups.size(); ++i) {
-      if (c[i] > 0 && e[i] == 0) return false;
-      more += groups[i].nrows * (c[i] - e[i]);
-    }
-    return more <= 0;
+    for (size_t i = 0; i < groups.size(); ++i) more += is[i] - was[i];
+    return spare >= 0 && more <= 0;
   };
   even_splits.order();
   Work* work = &even_splits;
@@ -590,21 +636,16 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // Even splits that fit one round of slots are balanced to the rounding of a tile: only
   // lists of more items are cut (24 fp32 row blocks of 256 rows, 4 to 16 tiles each, ran
   // 60 us in pieces of one and two tiles and 99 us cut into pieces of up to four).
-  // Their pieces are held in fp32, as the accumulators of a whole row block are (in bf16 the
-  // error against 64 bits of 288 row blocks that were whole, 18 requests of 174 tokens, was
-  // 0.0052; whole and in fp32 it is 0.0050).  Where that does not fit the static scratch
-  // that the even splits fit, 16 bits serve if they round no more than the even splits' do
-  // (int8 ragged batch of 3: 0.00569 in both lists); else the even splits stay.
   if (!sif && o.kv_splits == 0 && int64_t(even_splits.items.size()) > target) {
-    auto fits = [&](const Work& wk) { return layout(wk).total <= C2KV_STATIC_SCRATCH_BYTES; };
     by_slot = cut_by_slot();
+    // (rows that exist, to the 16 that a workgroup of the merge kernel reads: 4 of 64 in a
+    // decode step)
+    by_slot.part_rows = static_cast<int32_t>(std::min<int64_t>(RB, (R + 15) / 16 * 16));
+    const bool allowed = act_bytes == 4
+                             ? layout(by_slot).total <= C2KV_STATIC_SCRATCH_BYTES ||
+                                   layout(even_splits).total > C2KV_STATIC_SCRATCH_BYTES
+                             : widen_partials(by_slot, even_splits);
     by_slot.order();
-    by_slot.part_bytes = 4;
-    bool allowed = fits(by_slot) || !fits(even_splits);
-    if (!allowed && act_bytes == 2) {
-      by_slot.part_bytes = 2;
-      allowed = fits(by_slot) && rounds_no_more(by_slot, even_splits);
-    }
     if (allowed && makespan(by_slot) < kCutGain * makespan(even_splits)) work = &by_slot;
   }
   // The last split of a row block to finish merges it where that takes one workgroup
@@ -615,20 +656,20 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // 256 rows in 2-3 splits 41.0 -> 36.6 us, decode batch of 24 in 4 splits
   // 76.8 -> 75.6, 96 decode row blocks in 4 splits (one round) 9.9 -> 9.1; but 84 blocks of
   // 64 rows in 5 splits, one round, 28.0 -> 29.2, 18 splits of 256 rows 16.0 -> 33.3.
-  int64_t merge_bytes = 0;
-  for (const MergeGroup& m : work->merges)
-    merge_bytes = std::max(merge_bytes, int64_t(m.nsplit) * m.nrows * D * work->part_bytes);
+  int64_t most_bytes = 0;
+  for (const MergeGroup& m : work->merges) most_bytes = std::max(most_bytes, merge_bytes(m));
   p.merge_in_kernel =
       o.merge_mode == 1 ||
       (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
-       (int64_t(work->items.size()) > target || merge_bytes <= kFewMergeBytes));
+       (int64_t(work->items.size()) > target || most_bytes <= kFewMergeBytes));
 
   p.ws = layout(*work);
   p.items = std::move(work->items);
   p.merges = std::move(work->merges);
   p.n_partials = work->n_partials;
   p.max_splits = work->max_splits;
-  p.part_f32 = work->part_bytes == 4;
+  p.part_rows = work->part_rows;
+  for (const MergeGroup& m : p.merges) p.part_f32 |= m.f32 != 0;
 
   // ---- workspace image --------------------------------------------------------
   const WorkspaceLayout& w = p.ws;

@@ -28,12 +28,15 @@ struct WorkItem {
   int32_t page0;                       // request b's first page (its pages are consecutive)
   int32_t n_ranges;                    // 0: tiles [tile0, tile1); else item position
   int32_t rng[3];                      // i < tile1 runs through ranges [first, end) given
-  int32_t pad;                         // as first | end << 16 (multi-range SIF items)
+                                       // as first | end << 16 (multi-range SIF items)
+  int32_t part_f32;                    // 1: the partial is fp32 beside bf16 activations
 };
 
-// Row block whose key splits are combined by the merge kernel.
+// Row block whose key splits are combined, by the merge kernel or by the last split's
+// workgroup.  Split k is partial part0 + k, or, where they are fp32 beside bf16
+// activations (f32), the two partials from part0 + 2 k.
 struct MergeGroup {
-  int32_t b, g, row0, nrows, part0, nsplit, pad0, pad1;
+  int32_t b, g, row0, nrows, part0, nsplit, f32, pad;
 };
 
 // Byte offsets of the device tables inside the workspace.
@@ -49,8 +52,8 @@ struct WorkspaceLayout {
   size_t merges = 0;      // MergeGroup [n_merge]
   size_t counters = 0;    // int32 [n_merge], zero between launches
   size_t table_bytes = 0; // end of the tables (uploaded image size)
-  size_t part_o = 0;      // activation dtype (fp32 if part_f32) [n_partials][rows_per_block][D]
-  size_t part_lse = 0;    // float [n_partials][rows_per_block]
+  size_t part_o = 0;      // activation dtype [n_partials][part_rows][D]
+  size_t part_lse = 0;    // float [n_partials][part_rows]
   size_t total = 0;
 };
 
@@ -85,7 +88,8 @@ struct Plan {
   std::vector<WorkItem> items;
   std::vector<MergeGroup> merges;
   int32_t n_partials = 0, max_splits = 1;
-  bool part_f32 = false;          // partials in fp32 whatever the activation dtype
+  int32_t part_rows = 128;        // rows of a partial: a multiple of 16, up to rows_per_block
+  bool part_f32 = false;          // some row blocks' partials are fp32 beside bf16 activations
   bool merge_in_kernel = false;   // last split of a row block merges (else a merge kernel)
 
   // tables in float (host image)

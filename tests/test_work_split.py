@@ -55,6 +55,19 @@ def test_one_round_of_even_splits_is_kept():
     assert 200 < i["n_work_items"] <= 256, i
 
 
+def test_decode_partials_hold_the_rows_that_exist():
+    """560 decode row blocks of 4 rows on 512 slots, whole by equal splits, are cut: their
+    fp32 pieces take 16 of a row block's 64 rows, and so fit the static scratch."""
+    n, b = 3700, 70
+    plan = c2kv.Plan(32, 8, 128, "bf16", 5e5, np.arange(b + 1, dtype=np.int32),
+                     np.zeros(b, np.int64), np.full(b, n, np.int32), np.zeros(b, np.int32),
+                     n * np.arange(b + 1, dtype=np.int32), np.tile(np.arange(n, dtype=np.int32), b),
+                     1)
+    i = plan.info
+    assert i["rows_per_block"] == 64 and i["n_merge_groups"] > 0 and i["n_work_items"] > 560, i
+    assert i["workspace_bytes"] <= c2kv.STATIC_SCRATCH_BYTES
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,num_cus", CASES)
 def test_cut_row_blocks_parity(shape, num_cus):
@@ -87,3 +100,27 @@ def test_cut_row_blocks_round_once(shape, num_cus):
     paged, _, _, _, _ = run_paged(w, dev=dev, plan=plan)
     assert torch.equal(out, paged)
     assert np.abs(c2kv.to_numpy_f64(out) - ref).max() <= 2.0 ** -8 + 2e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,opts", [
+    # fp32 pieces of 64- and 256-row blocks, combined by the merge kernel
+    (CASES[0][0], dict(num_cus=8, merge_mode=2)),
+    (CASES[2][0], dict(num_cus=32, merge_mode=2)),
+    # more than 16 pieces of few rows: one row a workgroup
+    (dict(n_q_heads=4, n_kv_heads=1, batch=3, chunks_per_req=4, chunk_len=3500, suffix_len=3,
+          seed=0), dict(num_cus=37)),
+    # 96 row blocks in 256 pieces, which fit the static scratch only with some in bf16
+    (dict(n_q_heads=8, n_kv_heads=8, batch=4, chunks_per_req=1, chunk_len=310, prefix_len=0,
+          keep=("ratio", 0.9, 1.0), suffix_len=744, seed=5), dict(merge_mode=1)),
+    (dict(n_q_heads=8, n_kv_heads=8, batch=4, chunks_per_req=1, chunk_len=310, prefix_len=0,
+          keep=("ratio", 0.9, 1.0), suffix_len=744, seed=5), dict(merge_mode=2)),
+])
+def test_fp32_pieces_parity(shape, opts):
+    from test_gpu_parity import _both_paths
+    w = synth.small(**dict(dict(seed=31, keep=("ratio", 0.4, 0.95)), **shape))
+    i = _both_paths(w, f"fp32 pieces {shape}", **opts).info
+    rows = min(i["rows_per_block"], -(-w.suffix_len * w.n_q_heads // w.n_kv_heads // 16) * 16)
+    bf16 = i["n_work_items"] * rows * w.head_dim * 2
+    assert i["n_merge_groups"] > 0 and bf16 < i["workspace_bytes"] <= c2kv.STATIC_SCRATCH_BYTES
+    assert (i["max_splits"] > 16) == (shape.get("chunk_len") == 3500)

@@ -73,17 +73,21 @@ int main(int argc, char** argv) {
         const MergeGroup& m = p.merges[v[i].merge];
         CHECK(m.b == v[i].b && m.g == v[i].g && m.row0 == v[i].row0 && m.nrows == rows);
         CHECK(m.nsplit == int(v.size()) && m.nsplit <= p.max_splits && m.nsplit <= kMaxSplits);
-        CHECK(v[i].partial == m.part0 + int(i) && partials.insert(v[i].partial).second);
+        CHECK(v[i].partial == m.part0 + (int(i) << m.f32) && v[i].part_f32 == m.f32);
+        for (int k = 0; k <= m.f32; ++k) CHECK(partials.insert(v[i].partial + k).second);
       }
     }
     CHECK(int(partials.size()) == p.n_partials);
     // with at least one row block per slot, equal splits leave all of them whole
     const int cu = o.num_cus > 0 ? o.num_cus : 256;
     if (int(blocks.size()) >= cu * (RB == 64 ? 2 : 1) && !p.merges.empty()) {
-      CHECK(p.part_f32);
+      for (const MergeGroup& m : p.merges) CHECK(m.f32 || cfg.act_dtype == C2KV_F32);
       ++whole;
     }
-    CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * RB <= p.ws.total);
+    CHECK(p.part_rows % 16 == 0 && p.part_rows <= RB && p.part_rows >= std::min(R, RB));
+    CHECK(p.ws.part_o + size_t(cfg.act_dtype == C2KV_F32 ? 4 : 2) * p.n_partials * p.part_rows *
+              cfg.head_dim <= p.ws.part_lse);
+    CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * p.part_rows <= p.ws.total);
     if (sizes.size() > 1 && *sizes.rbegin() <= 8) ++cut;
   }
   std::printf("ok %d cut %d whole %d\n", iters, cut, whole);
