@@ -384,6 +384,8 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
   constexpr int CPR = D / EPT;                  // chunks per row
   const int units = mg.nrows * CPR, ns = mg.nsplit;
   constexpr int US = sizeof(PT) / sizeof(T);    // partials a split takes
+  constexpr int kPastEnd = 1 << 30;             // a group's partials are at most 32 MiB
+  static_assert(kMaxSplits * 256 * D * sizeof(PT) <= kPastEnd, "past every group's partials");
   const float* pl = a.part_lse + size_t(mg.part0) * a.PR;
   const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(
       static_cast<T*>(a.part_o) + size_t(mg.part0) * a.PR * D, 0,
@@ -424,17 +426,20 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
     for (int i = i0; i < ns; i += NB * istep) {
       float l[UB][NB];
       uint32_t w[UB][NB][4];
-      // unconditional loads from clamped indices; splits past the last get weight 0
+      // unconditional loads: the LSE of a split past the last from a clamped index (it is
+      // replaced by -inf), its row from past the buffer's end, which reads as zero without
+      // a memory access (weight 0 times an infinity of the last split's row would be NaN)
 #pragma unroll
       for (int k = 0; k < UB; ++k) {
         const int u = min(u0 + k * ustep, units - 1);
         const int rloc = u / CPR;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          const int sp = min(i + j * istep, ns - 1);
-          l[k][j] = load_shared(pl + size_t(sp * US) * a.PR + rloc);
+          const int sp = i + j * istep;
+          l[k][j] = load_shared(pl + size_t(min(sp, ns - 1) * US) * a.PR + rloc);
+          const int at = sp < ns ? sp * a.PR * D * int(sizeof(PT)) : kPastEnd;
           const auto x = __builtin_amdgcn_raw_buffer_load_b128(
-              po, ((sp * a.PR + rloc) * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
+              po, at + (rloc * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
           w[k][j][0] = x[0]; w[k][j][1] = x[1]; w[k][j][2] = x[2]; w[k][j][3] = x[3];
         }
       }

@@ -1,7 +1,9 @@
 """The merge of a row block's splits by the workgroup that finishes last: few rows (the
 splits spread over sets of threads, one batch and several) and many (chunks in batches of
 four), at the edges between the two, for both element sizes and head sizes.  Repeated
-launches find the arrival counters at zero again."""
+launches find the arrival counters at zero again.  An infinite value of the last split stays
+infinite."""
+import numpy as np
 import pytest
 import torch
 
@@ -35,3 +37,31 @@ def test_merge_in_kernel(heads, suffix_len, rows_per_block, head_dim, dtype, kv_
     for _ in range(3):
         out, l2, _, _ = run_fused(w, dev=dev, plan=plan)
         assert torch.equal(out, first) and torch.equal(l2, lse)
+
+
+@pytest.mark.parametrize("heads,suffix_len,rows_per_block,dtype,kv_splits", [
+    (4, 2, 64, "bf16", 3),            # splits spread over sets of threads
+    (4, 2, 64, "f32", 2),
+    (4, 25, 128, "bf16", 2),          # batches of four chunks and four splits
+    (4, 61, 256, "bf16", 5),
+    (3, 20, 64, "f32", 3),
+])
+def test_infinite_value_stays_infinite(heads, suffix_len, rows_per_block, dtype, kv_splits):
+    """A value of +Inf at the first new token (which every row sees, in the last split)
+    makes that channel +Inf in every row, and no other channel: no load that only fills a
+    batch may meet it with weight 0."""
+    w = synth.small(pool_dtype=dtype, n_q_heads=2 * heads, n_kv_heads=2, batch=2,
+                    chunks_per_req=4, chunk_len=700, keep=("ratio", 0.8, 0.9),
+                    suffix_len=suffix_len, seed=72)
+    v = (w.v_suf if dtype == "f32" else synth.bf16_bits_to_f32(w.v_suf)).copy()
+    v[:, 0, :, 5] = np.inf
+    w = synth.with_overrides(w, v_suf=synth.cast_f64(v, w.act_dtype))
+    for mode in (2, 1):
+        out, _, plan, _ = run_fused(w, rows_per_block=rows_per_block, kv_splits=kv_splits,
+                                    merge_mode=mode)
+        assert plan.info["max_splits"] == kv_splits
+        out = out.float()
+        inf = torch.zeros_like(out, dtype=torch.bool)
+        inf[..., 5] = True
+        assert torch.equal(torch.isposinf(out), inf), mode
+        assert torch.isfinite(out[~inf]).all(), mode
