@@ -373,10 +373,13 @@ __device__ inline float load_shared(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Each thread takes 16-byte chunks of the rows.  With chunks for all threads, UB of
-// them at a time over batches of NB splits; with fewer (decode), the splits are also
-// spread over `lanes` sets of threads, combined through LDS (`xs`).  Bound by the
-// latency of the loads, which are all in flight within a batch.
+// Each thread takes 16-byte chunks of the rows.  With more chunks than threads, UB of
+// them at a time over batches of four splits; with fewer, one a thread over batches of
+// eight, and where the threads allow it (decode) the splits are also spread over `lanes`
+// sets of them, combined through LDS (`xs`).  Bound by the latency of the loads, which are
+// all in flight within a batch.  (Row blocks of 9 to 16 rows, 144 to 256 chunks for 256
+// threads, took four chunks a thread, most of them copies of the last: 40 blocks of 16 rows
+// in 5 splits 12.1 -> 10.6 us, 96 blocks of 12 rows in 5 splits 15.8 -> 14.4.)
 template <typename T, typename PT, int D, int NT>
 __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnParams& a, float* xs,
                                              int tid) {
@@ -428,16 +431,18 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
       uint32_t w[UB][NB][4];
       // unconditional loads: the LSE of a split past the last from a clamped index (it is
       // replaced by -inf), its row from past the buffer's end, which reads as zero without
-      // a memory access (weight 0 times an infinity of the last split's row would be NaN)
+      // a memory access (weight 0 times an infinity of the last split's row would be NaN);
+      // so too the chunks past the last
 #pragma unroll
       for (int k = 0; k < UB; ++k) {
+        const bool exists = u0 + k * ustep < units;
         const int u = min(u0 + k * ustep, units - 1);
         const int rloc = u / CPR;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           const int sp = i + j * istep;
           l[k][j] = load_shared(pl + size_t(min(sp, ns - 1) * US) * a.PR + rloc);
-          const int at = sp < ns ? sp * a.PR * D * int(sizeof(PT)) : kPastEnd;
+          const int at = exists && sp < ns ? sp * a.PR * D * int(sizeof(PT)) : kPastEnd;
           const auto x = __builtin_amdgcn_raw_buffer_load_b128(
               po, at + (rloc * D + (u % CPR) * EPT) * int(sizeof(PT)), 0, kAgentScope);
           w[k][j][0] = x[0]; w[k][j][1] = x[1]; w[k][j][2] = x[2]; w[k][j][3] = x[3];
@@ -475,7 +480,7 @@ __device__ __forceinline__ void merge_splits(const MergeGroup& mg, const AttnPar
       }
     }
   };
-  if (2 * units > NT) {
+  if (units > NT) {
     constexpr int UB = 4;
     float mx[UB], z[UB], acc[UB][EPT];
     for (int u0 = tid; u0 < units; u0 += UB * NT) {

@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
     (4, 1, 64, 128, "bf16", 33),      # 4 rows, splits past one batch of each lane
     (4, 1, 64, 64, "f32", 9),
     (4, 2, 64, 128, "bf16", 17),      # 8 rows: 128 chunks, the most that spread over lanes
-    (3, 3, 64, 128, "bf16", 5),       # 9 rows: 144 chunks, batches of four chunks
+    (3, 3, 64, 128, "bf16", 5),       # 9 rows: 144 chunks, one a thread
+    (4, 4, 64, 128, "bf16", 9),       # 16 rows: 256 chunks, a thread each, two batches
+    (1, 17, 64, 128, "bf16", 9),      # 17 rows: 272 chunks, batches of four chunks
     (1, 17, 128, 64, "bf16", 5),      # 17 rows of 8 chunks, 512 threads
     (4, 25, 128, 128, "i8", 4),
     (4, 64, 256, 128, "bf16", 5),     # 256 rows, a second batch of one split
