@@ -889,8 +889,9 @@ struct TileLoader {
 // every 64-key tile, keep their own online softmax, and the two halves are
 // combined through LDS at the end.  256-thread workgroups (64-row blocks) run two
 // to a CU, so that two work items' latencies overlap.  MERGE: the last split of a row
-// block merges it where the plan says so (kernels of their own: the merge raises the
-// registers of some, and SIF extraction measured 1.1 % slower with it behind a branch).
+// block merges it where the plan says so.  Plans that merge nothing, or in a launch of its
+// own, run kernels without it, which take fewer registers (extraction of head size 64
+// 70.2 -> 69.6 us, ragged batch 108.2 -> 107.7; others within the runs of one side).
 // P32: some row blocks' partials are fp32 beside bf16 tiles (WorkItem::part_f32).
 template <typename T, int D, int SRC, int KG, int NT, bool MERGE, bool P32>
 __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {

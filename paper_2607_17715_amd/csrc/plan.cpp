@@ -659,9 +659,10 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   int64_t most_bytes = 0;
   for (const MergeGroup& m : work->merges) most_bytes = std::max(most_bytes, merge_bytes(m));
   p.merge_in_kernel =
-      o.merge_mode == 1 ||
-      (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
-       (int64_t(work->items.size()) > target || most_bytes <= kFewMergeBytes));
+      !work->merges.empty() &&        // (plans that merge nothing run the smaller kernels)
+      (o.merge_mode == 1 ||
+       (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
+        (int64_t(work->items.size()) > target || most_bytes <= kFewMergeBytes)));
 
   p.ws = layout(*work);
   p.items = std::move(work->items);

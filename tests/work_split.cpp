@@ -1,9 +1,10 @@
 // Checks the attention work list of ragged batches (plan.cpp, host code only):
 // the items of every row block cover its key tiles exactly once, in order, each
 // split with a partial of its own inside its merge group.
-// Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n> whole <m>" (cut: plans
-// with row blocks split in unequal numbers of pieces, though no count was asked for; whole:
-// cut plans whose row blocks equal splits would all leave whole).
+// Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n> whole <m> unmerged <k>"
+// (cut: plans with row blocks split in unequal numbers of pieces, though no count was asked
+// for; whole: cut plans whose row blocks equal splits would all leave whole; unmerged: plans,
+// with extraction plans, that merge nothing, and so run the kernels without a merge).
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -19,7 +20,7 @@ int main(int argc, char** argv) {
   const int iters = argc > 1 ? atoi(argv[1]) : 300;
   std::mt19937_64 rng(argc > 2 ? atoll(argv[2]) : 1);
   auto U = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
-  int cut = 0, whole = 0;
+  int cut = 0, whole = 0, unmerged = 0;
   for (int it = 0; it < iters; ++it) {
     c2kv_attn_cfg cfg{};
     const int hk[] = {1, 2, 4, 8}, G[] = {1, 3, 4, 8};
@@ -52,6 +53,20 @@ int main(int argc, char** argv) {
     Plan p;
     std::string err;
     CHECK(build_plan(cfg, d, S, &o, p, err) == C2KV_OK);
+
+    if (p.merges.empty()) CHECK(!p.merge_in_kernel);
+    o.merge_mode = U(0, 2);
+    Plan asked;
+    CHECK(build_plan(cfg, d, S, &o, asked, err) == C2KV_OK);
+    CHECK(asked.merges.size() == p.merges.size());
+    if (o.merge_mode > 0)
+      CHECK(asked.merge_in_kernel == (o.merge_mode == 1 && !p.merges.empty()));
+    // extraction: one item a row block, nothing to merge unless the grid is nearly empty
+    const int n_tok = U(64, 700);
+    Plan sif;
+    CHECK(build_sif_plan(cfg, B, n_tok, U(1, 16), U(0, 20), &o, sif, err) == C2KV_OK);
+    CHECK(!(sif.merges.empty() && sif.merge_in_kernel));
+    unmerged += p.merges.empty() + sif.merges.empty();
 
     const int g = cfg.n_q_heads / cfg.n_kv_heads, R = g * S, RB = p.rows_per_block;
     std::map<std::tuple<int, int, int>, std::vector<WorkItem>> blocks;
@@ -90,6 +105,6 @@ int main(int argc, char** argv) {
     CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * p.part_rows <= p.ws.total);
     if (sizes.size() > 1 && *sizes.rbegin() <= 8) ++cut;
   }
-  std::printf("ok %d cut %d whole %d\n", iters, cut, whole);
+  std::printf("ok %d cut %d whole %d unmerged %d\n", iters, cut, whole, unmerged);
   return 0;
 }
