@@ -157,9 +157,9 @@ typedef struct c2kv_plan_opts {
                               than 64 rows) or 64                               */
   int32_t num_cus;         /* compute units to size the work list for (256)       */
   int32_t merge_mode;      /* combining key splits: 0 automatic (1 for few splits
-                              per row block, else 2), 1 the last split of a row
-                              block merges inside the attention kernel, 2 a
-                              separate merge kernel                               */
+                              of few bytes or beside other work, else 2), 1 the
+                              last split of a row block merges inside the attention
+                              kernel, 2 a separate merge kernel                   */
 } c2kv_plan_opts;
 
 /* The stored caches KV_reuse (Section 2.2, Eq. 2): device memory, caller-owned. */

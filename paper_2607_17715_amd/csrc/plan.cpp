@@ -52,10 +52,9 @@ constexpr int32_t kMinPiece = 2;      // shortest piece of a row block cut by sl
 // left the attention at 107-108 us and added a merge of 4-7 us).
 constexpr double kCutGain = 0.95;
 
-// Row blocks merged inside the attention kernel: splits, and bytes of their partials
-// where no other round of items hides it.
+// Row blocks merged inside the attention kernel: splits where they are few bytes.
 constexpr int32_t kFewSplits = 5;
-constexpr int64_t kFewMergeBytes = 48 << 10;
+constexpr int64_t kFewMergeBytes = 16 << 10;
 
 // A work list: items, by the XCD that runs them, and the row blocks to merge.
 struct Work {
@@ -648,21 +647,33 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     by_slot.order();
     if (allowed && makespan(by_slot) < kCutGain * makespan(even_splits)) work = &by_slot;
   }
-  // The last split of a row block to finish merges it where that takes one workgroup
-  // little (few splits), and either other workgroups run meanwhile (more than one
-  // round of items) or the partials are few bytes.  Else it is a tail that one
-  // workgroup per row block runs alone, and a separate launch spreads the rows over the
-  // machine.  Measured, separate kernel -> in the attention kernel: 143 row blocks of
-  // 256 rows in 2-3 splits 41.0 -> 36.6 us, decode batch of 24 in 4 splits
-  // 76.8 -> 75.6, 96 decode row blocks in 4 splits (one round) 9.9 -> 9.1; but 84 blocks of
-  // 64 rows in 5 splits, one round, 28.0 -> 29.2, 18 splits of 256 rows 16.0 -> 33.3.
+  // The last split of a row block to finish merges it where that takes its workgroup
+  // little: the launch of a kernel saved is then more than the tail.  Else the merge is a
+  // tail that one workgroup per row block runs alone, and a separate launch spreads the
+  // rows over the machine.  Taken in bf16 where
+  //  - a row block's partials are few bytes, in up to five splits.  Measured launched one
+  //    by one, separate -> in the attention kernel: 16 blocks of 4 rows in 5 splits 11.2 ->
+  //    8.5 us, 48 of 16 in 4 11.3 -> 10.0 (replayed from a graph 9.6 -> 10.0), 96 of 12 in 5
+  //    14.3 -> 14.4; but 40 of 16 in 5 (20 KB) 10.2 -> 10.6 (9.8 -> 10.7), 44 of 32 in 5
+  //    11.4 -> 12.4, 16 of 12 in 12 10.9 -> 9.8 (8.5 -> 9.9);
+  //  - more than one round of items runs, in up to three splits (four of half the bytes at
+  //    head size 64), and most row blocks are split, so that other workgroups run beside
+  //    most merges: 96 of 96 blocks in 4 38.6 -> 34.7 us at head size 64, 191 of 192 of 256
+  //    rows in 2 splits 43.8 -> 36.4 us, 160 in 3 130.2 -> 128.4, 219 of 288 of 128 rows
+  //    49.9 -> 44.9; but 111 of 192 in 2 37.8 -> 45.9, 88 in 4 38.8 -> 41.7, 66 in 5
+  //    58.3 -> 64.1, 40 in 6 30.1 -> 38.0, 24 in 12 95.9 -> 116.5.  Not for extraction,
+  //    whose splits are of one to three tiles: 112 blocks in 3 39.6 -> 42.8.
+  // In fp32, whose kernels are bound by their products, it gains little or loses: 120 blocks
+  // of 256 rows in 3 splits 370 -> 364, 144 in 2 85.1 -> 87.1, 16 of 6 rows in 4 15.1 -> 15.3.
   int64_t most_bytes = 0;
   for (const MergeGroup& m : work->merges) most_bytes = std::max(most_bytes, merge_bytes(m));
+  const bool few = work->max_splits <= kFewSplits && most_bytes <= kFewMergeBytes;
+  const bool hidden = !sif && work->max_splits <= (D == 64 ? 4 : 3) &&
+                      int64_t(work->items.size()) > target &&
+                      4 * work->merges.size() >= 3 * groups.size();
   p.merge_in_kernel =
       !work->merges.empty() &&        // (plans that merge nothing run the smaller kernels)
-      (o.merge_mode == 1 ||
-       (o.merge_mode == 0 && work->max_splits <= kFewSplits &&
-        (int64_t(work->items.size()) > target || most_bytes <= kFewMergeBytes)));
+      (o.merge_mode == 1 || (o.merge_mode == 0 && act_bytes == 2 && (few || hidden)));
 
   p.ws = layout(*work);
   p.items = std::move(work->items);

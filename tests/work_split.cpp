@@ -16,12 +16,42 @@
 #include "plan.hpp"
 using namespace c2kv;
 #define CHECK(c) do { if (!(c)) { std::printf("FAIL %s line %d iter %d\n", #c, __LINE__, it); return 1; } } while (0)
+// Whether the plan of `batch` requests of 4096 tokens, 4 query heads a kv-head, has row
+// blocks merged in the attention kernel.
+static bool in_kernel(int batch, int kv_heads, int suffix, int splits, c2kv_dtype dtype) {
+  c2kv_attn_cfg cfg{};
+  cfg.n_kv_heads = kv_heads;
+  cfg.n_q_heads = 4 * kv_heads;
+  cfg.head_dim = 128;
+  cfg.act_dtype = dtype;
+  cfg.rope_base = 1e4;
+  c2kv_plan_opts o{};
+  o.kv_splits = splits;
+  std::vector<int32_t> off, zero(batch, 0), span(batch, 4096), koff, kept;
+  std::vector<int64_t> row0(batch, 0);
+  for (int b = 0; b <= batch; ++b) { off.push_back(b); koff.push_back(4096 * b); }
+  for (int i = 0; i < 4096 * batch; ++i) kept.push_back(i % 4096);
+  c2kv_compose_desc d{};
+  d.batch = d.n_segments = batch; d.req_seg_off = off.data();
+  d.seg_row0 = row0.data(); d.seg_span = span.data(); d.seg_orig_pos0 = zero.data();
+  d.seg_kept_off = koff.data(); d.kept_idx = kept.data();
+  Plan p;
+  std::string err;
+  if (build_plan(cfg, d, suffix, &o, p, err) != C2KV_OK) std::abort();
+  return p.merge_in_kernel;
+}
 int main(int argc, char** argv) {
   const int iters = argc > 1 ? atoi(argv[1]) : 300;
   std::mt19937_64 rng(argc > 2 ? atoll(argv[2]) : 1);
   auto U = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
-  int cut = 0, whole = 0, unmerged = 0;
-  for (int it = 0; it < iters; ++it) {
+  int cut = 0, whole = 0, unmerged = 0, it = -1;
+  // few bytes, more bytes, fp32; more than one round in few and in more splits, one round
+  CHECK(in_kernel(2, 8, 1, 5, C2KV_BF16) && in_kernel(6, 8, 4, 4, C2KV_BF16));
+  CHECK(!in_kernel(5, 8, 4, 5, C2KV_BF16) && !in_kernel(2, 8, 1, 8, C2KV_BF16));
+  CHECK(!in_kernel(2, 8, 1, 4, C2KV_F32));
+  CHECK(in_kernel(12, 8, 64, 3, C2KV_BF16) && !in_kernel(12, 8, 64, 4, C2KV_BF16));
+  CHECK(!in_kernel(8, 8, 64, 3, C2KV_BF16));
+  for (it = 0; it < iters; ++it) {
     c2kv_attn_cfg cfg{};
     const int hk[] = {1, 2, 4, 8}, G[] = {1, 3, 4, 8};
     cfg.n_kv_heads = hk[U(0, 3)];
