@@ -1329,9 +1329,13 @@ __global__ __launch_bounds__(NT, 2) void attn_kernel(AttnParams a) {
   // Wavefronts 4-7 of a 512-thread workgroup (the second on each SIMD) prepare the next
   // tile after this one's products, the others before them: with all eight in one order,
   // a tile cost its loader's VALU work, then its products and softmax, one after the
-  // other (ragged batch 117.1 -> 110.4 us, int8 layer 24.1 -> 23.2).  Not for fp32, whose
-  // loader is little beside its products and whose 256-row kernels spill.
-  const bool late = NT == 512 && sizeof(T) == 2 && __builtin_amdgcn_readfirstlane(wave) >= 4;
+  // other.  All loops but the paged one do so: pool tiles (ragged batch 117.1 -> 110.4 us,
+  // int8 layer 24.1 -> 23.2), suffix tiles (2048 new tokens over 2048 pages' tokens 88.4 ->
+  // 83.3) and extraction (4 x 2048 tokens 208.3 -> 203.9), there without the splits of a
+  // row block, which are few tiles (88 row blocks in 3 splits with it 30.9, without 30.3).
+  // Not for fp32, whose loader is little beside its products and whose 256-row kernels spill.
+  const bool late = NT == 512 && sizeof(T) == 2 && (!kSif || it.partial < 0) &&
+                    __builtin_amdgcn_readfirstlane(wave) >= 4;
 
   // in the paged loop below, a wavefront whose row group is empty (decode: 4
   // rows in a 128-row block) still loads and commits its share of each tile
