@@ -516,17 +516,20 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // nearly empty one, 182 -> 135 us; 192 decode row blocks of 59 tiles in three
   // splits on 512 slots, 86.5 -> 73.6 us.
   const int64_t tile_cost = cfg.act_dtype == C2KV_F32 ? kF32TileCost : 1;
+  const int64_t work_all = total_tiles * tile_cost + kItemTiles * int64_t(groups.size());
   struct Piece { int32_t end; int64_t slot; };       // of a row block, from the last one's end
   std::vector<std::vector<Piece>> pieces;
-  auto fill_slots = [&](int64_t load) {              // the number of slots taken
-    pieces.assign(groups.size(), {});
+  // the number of slots taken; the pieces are kept where `keep` says so
+  auto fill_slots = [&](int64_t load, bool keep) {
     int64_t slot = 0, room = load;
-    for (size_t i = 0; i < groups.size(); ++i)
+    for (size_t i = 0; i < groups.size(); ++i) {
+      int32_t count = 0;
       for (int32_t t = 0; t < groups[i].tiles;) {
         const int32_t left = groups[i].tiles - t;
-        int64_t n = std::min<int64_t>(left, (room - kItemTiles) / tile_cost);
+        const int64_t fits = room - kItemTiles;
+        int64_t n = std::min<int64_t>(left, tile_cost == 1 ? fits : fits / tile_cost);
         if (n < left && left - n < kMinPiece) n = left - kMinPiece;
-        if (int32_t(pieces[i].size()) == kMaxSplits - 1) n = left;
+        if (count == kMaxSplits - 1) n = left;
         if (n < std::min(left, kMinPiece)) {
           ++slot;
           room = load;
@@ -534,20 +537,35 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
         }
         t += static_cast<int32_t>(n);
         room -= n * tile_cost + kItemTiles;
-        pieces[i].push_back({t, slot});
+        ++count;
+        if (keep) pieces[i].push_back({t, slot});
       }
+    }
     return slot + 1;
   };
   auto cut_by_slot = [&]() {
     Work wk;
-    int64_t lo = kItemTiles + 2 * kMinPiece * tile_cost;
-    int64_t hi = std::max(lo, total_tiles * tile_cost + kItemTiles * int64_t(groups.size()));
+    // the least load that fills no more than the slots: from the mean load up, in steps
+    // that double, then by halves
+    int64_t lo = std::max<int64_t>(kItemTiles + 2 * kMinPiece * tile_cost, work_all / target);
+    int64_t step = 1;
+    while (fill_slots(lo + step - 1, false) > target) {
+      lo += step;
+      step *= 2;
+    }
+    int64_t hi = lo + step - 1;
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
-      if (fill_slots(mid) <= target) hi = mid;
+      if (fill_slots(mid, false) <= target) hi = mid;
       else lo = mid + 1;
     }
-    const int64_t n_slots = fill_slots(lo);
+    pieces.resize(groups.size());
+    const int64_t n_slots = fill_slots(lo, true);
+    size_t n_items = 0;
+    for (const auto& pcs : pieces) n_items += pcs.size();
+    wk.items.reserve(n_items);
+    wk.merges.reserve(groups.size());
+    for (auto& q : wk.queue) q.reserve(n_items / kXcds + kXcds);
     for (size_t i = 0; i < groups.size(); ++i) {
       const Group& gr = groups[i];
       const int32_t merge = wk.add_merge(gr.b, gr.g, gr.row0, gr.nrows, int32_t(pieces[i].size()));
@@ -566,8 +584,8 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   };
   // Time of a work list in bf16 key tiles: each XCD's slots taken in the grid's order, and
   // the merge (its launch, and its partials written and read).
+  const size_t slots = static_cast<size_t>(std::max<int64_t>(1, target / kXcds));
   auto makespan = [&](const Work& wk) {
-    const size_t slots = static_cast<size_t>(std::max<int64_t>(1, target / kXcds));
     double worst = 0;
     for (size_t x = 0; x < size_t(kXcds); ++x) {
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
@@ -635,7 +653,12 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
   // Even splits that fit one round of slots are balanced to the rounding of a tile: only
   // lists of more items are cut (24 fp32 row blocks of 256 rows, 4 to 16 tiles each, ran
   // 60 us in pieces of one and two tiles and 99 us cut into pieces of up to four).
-  if (!sif && o.kv_splits == 0 && int64_t(even_splits.items.size()) > target) {
+  // (Nor is a list built where even its whole row blocks, spread without a remainder, would
+  // not be short enough: many rounds of items, 1264 row blocks 5 ms of a plan's 23.)
+  const double even_time = makespan(even_splits) * kCutGain;
+  const double spread = double(work_all) / double(kXcds * slots);
+  if (!sif && o.kv_splits == 0 && int64_t(even_splits.items.size()) > target &&
+      spread < even_time) {
     by_slot = cut_by_slot();
     // (rows that exist, to the 16 that a workgroup of the merge kernel reads: 4 of 64 in a
     // decode step)
@@ -645,7 +668,7 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
                                    layout(even_splits).total > C2KV_STATIC_SCRATCH_BYTES
                              : widen_partials(by_slot, even_splits);
     by_slot.order();
-    if (allowed && makespan(by_slot) < kCutGain * makespan(even_splits)) work = &by_slot;
+    if (allowed && makespan(by_slot) < even_time) work = &by_slot;
   }
   // The last split of a row block to finish merges it where that takes its workgroup
   // little: the launch of a kernel saved is then more than the tail.  Else the merge is a
