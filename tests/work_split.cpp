@@ -2,9 +2,10 @@
 // the items of every row block cover its key tiles exactly once, in order, each
 // split with a partial of its own inside its merge group.
 // Usage: work_split <iterations> <seed>; prints "ok <plans> cut <n> whole <m> unmerged <k>"
-// (cut: plans with row blocks split in unequal numbers of pieces, though no count was asked
-// for; whole: cut plans whose row blocks equal splits would all leave whole; unmerged: plans,
-// with extraction plans, that merge nothing, and so run the kernels without a merge).
+// (cut: plans with a row block in pieces of lengths that differ by more than a tile, which
+// equal splits never do; whole: cut plans whose row blocks equal splits would all leave
+// whole; unmerged: plans, with extraction plans, that merge nothing, and so run the kernels
+// without a merge).
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -62,11 +63,14 @@ int main(int argc, char** argv) {
     c2kv_plan_opts o{};
     const int cus[] = {0, 8, 20, 256};
     o.num_cus = cus[U(0, 3)];
-    const int B = U(1, 12), S = U(0, 1) ? U(1, 4) : U(5, 300), most = U(0, 3) ? U(1, 6000) : 0;
+    int B = U(1, 12), S = U(0, 1) ? U(1, 4) : U(5, 300), most = U(0, 3) ? U(1, 6000) : 0;
+    // one long request among short ones: more pieces of it than a row block may have
+    const bool giant = it % 100 == 99;
+    if (giant) { B = 401; S = 1; cfg.n_q_heads = cfg.n_kv_heads = 1; o.num_cus = 256; }
     std::vector<int32_t> req_off(B + 1, 0), span, orig, koff{0}, kept;
     std::vector<int64_t> row0;
     for (int b = 0; b < B; ++b) {
-      const int n = most ? U(most / 3, most) : 0;
+      const int n = giant ? (b ? 100 : 200000) : most ? U(most / 3, most) : 0;
       if (n > 0) {
         row0.push_back(0);
         span.push_back(n);
@@ -102,16 +106,20 @@ int main(int argc, char** argv) {
     std::map<std::tuple<int, int, int>, std::vector<WorkItem>> blocks;
     for (const auto& w : p.items) blocks[{w.b, w.g, w.row0}].push_back(w);
     CHECK(int64_t(blocks.size()) == int64_t(B) * cfg.n_kv_heads * ((R + RB - 1) / RB));
-    std::set<int> partials, sizes;
+    std::set<int> partials;
+    int shortest = 1 << 30;
+    bool uneven = false;
     for (auto& kv : blocks) {
       auto& v = kv.second;
       std::sort(v.begin(), v.end(), [](const WorkItem& x, const WorkItem& y) { return x.tile0 < y.tile0; });
       const int n = p.req_slot0[v[0].b + 1] - p.req_slot0[v[0].b];
       const int rows = std::min(RB, R - v[0].row0), tmax = (v[0].row0 + rows - 1) / g;
       CHECK(v.front().tile0 == 0 && v.back().tile1 == (n + 63) / 64 + (tmax + 64) / 64);
-      sizes.insert(int(v.size()));
+      int lo = 1 << 30, hi = 0;
       for (size_t i = 0; i < v.size(); ++i) {
         CHECK(v[i].nrows == rows && v[i].tile0 < v[i].tile1);
+        lo = std::min(lo, v[i].tile1 - v[i].tile0);
+        hi = std::max(hi, v[i].tile1 - v[i].tile0);
         if (i) CHECK(v[i].tile0 == v[i - 1].tile1);
         if (v.size() == 1) { CHECK(v[i].partial == -1 && v[i].merge == -1); continue; }
         CHECK(v[i].merge >= 0 && v[i].merge < int(p.merges.size()));
@@ -121,6 +129,8 @@ int main(int argc, char** argv) {
         CHECK(v[i].partial == m.part0 + (int(i) << m.f32) && v[i].part_f32 == m.f32);
         for (int k = 0; k <= m.f32; ++k) CHECK(partials.insert(v[i].partial + k).second);
       }
+      uneven |= hi - lo > 1;
+      if (v.size() > 1) shortest = std::min(shortest, lo);
     }
     CHECK(int(partials.size()) == p.n_partials);
     // with at least one row block per slot, equal splits leave all of them whole
@@ -133,7 +143,7 @@ int main(int argc, char** argv) {
     CHECK(p.ws.part_o + size_t(cfg.act_dtype == C2KV_F32 ? 4 : 2) * p.n_partials * p.part_rows *
               cfg.head_dim <= p.ws.part_lse);
     CHECK(p.ws.part_lse + sizeof(float) * size_t(p.n_partials) * p.part_rows <= p.ws.total);
-    if (sizes.size() > 1 && *sizes.rbegin() <= 8) ++cut;
+    if (uneven) { CHECK(shortest >= 2); ++cut; }
   }
   std::printf("ok %d cut %d whole %d unmerged %d\n", iters, cut, whole, unmerged);
   return 0;
