@@ -33,7 +33,8 @@
  *     `c2kv_plan_create`.  Every other data pointer is a DEVICE pointer.
  *   Streams.  `stream` is a hipStream_t (NULL = the null stream).  Device work is
  *     enqueued asynchronously on it; no call synchronises the device.  Calls that
- *     share one plan (and so one workspace) must be ordered on one stream.
+ *     share one plan (and so one workspace, which holds the partials and arrival
+ *     counters of split row blocks) must be ordered on one stream.
  *   Errors.  Every call returns a c2kv_status and never aborts; the text of the
  *     last error on the calling thread is available from `c2kv_last_error`.
  *     C2KV_E_INVAL       bad argument (null pointer, shape, index, ordering);

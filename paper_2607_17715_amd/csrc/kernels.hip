@@ -540,7 +540,7 @@ struct TileLoader {
   // consecutive chunks of a key pair's rows, so that a load reads whole rows (4 key
   // pairs' rows a wavefront at D = 128) and a pair's int8 scales are one address.  A
   // wavefront's transposed words then lie in few columns of many rows: the 16-byte
-  // blocks of a value row are permuted by its index / 16 (vblock), which spreads them
+  // blocks of a value row are permuted by its index / 16 (vswap), which spreads them
   // over the banks and leaves the fragments' reads of 16 rows conflict-free.  (Kernels
   // over pages copy their transposed rows and keep a pair's chunks on one thread column.)
   // With a pair's chunks on 16 threads of eight wavefronts, every load touched 64 cache

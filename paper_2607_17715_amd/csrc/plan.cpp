@@ -426,9 +426,10 @@ c2kv_status build_plan(const c2kv_attn_cfg& cfg, const c2kv_compose_desc& d,
     return (size_t(x.b) * cfg.n_kv_heads + x.g) * n_rb + x.row0 / RB;
   };
 
-  // Key splits only add parallelism where the row blocks alone leave CUs idle;
-  // with at least one row block per CU they would only add partials, a merge
-  // and a second round of workgroups.
+  // Even splits: only where the row blocks alone leave slots idle.  With a row block per slot
+  // they would add partials, a merge and a second round of workgroups (256 row blocks of 34
+  // to 45 tiles: 151 us whole, 212 in two splits each); a remainder of row blocks past the
+  // last full round is what the cut by slot below is for.
   const bool split = int64_t(groups.size()) < target;
   const int64_t per_item =
       split ? std::max<int64_t>(1, (total_tiles + target - 1) / target) : INT32_MAX;
