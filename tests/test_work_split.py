@@ -121,10 +121,28 @@ def test_cut_row_blocks_round_once(shape, num_cus):
           keep=("ratio", 0.9, 1.0), suffix_len=744, seed=5), dict(merge_mode=2)),
 ])
 def test_fp32_pieces_parity(shape, opts):
+    from gpu_common import run_fused
     from test_gpu_parity import _both_paths
     w = synth.small(**dict(dict(seed=31, keep=("ratio", 0.4, 0.95)), **shape))
-    i = _both_paths(w, f"fp32 pieces {shape}", **opts).info
+    plan = _both_paths(w, f"fp32 pieces {shape}", **opts)
+    i = plan.info
     rows = min(i["rows_per_block"], -(-w.suffix_len * w.n_q_heads // w.n_kv_heads // 16) * 16)
     bf16 = i["n_work_items"] * rows * w.head_dim * 2
     assert i["n_merge_groups"] > 0 and bf16 < i["workspace_bytes"] <= c2kv.STATIC_SCRATCH_BYTES
     assert (i["max_splits"] > 16) == (shape.get("chunk_len") == 3500)
+    # the same bits from the static scratch, and from replays of a graph
+    ref, ref_lse, _, dev = run_fused(w, plan=plan)
+    out, lse = dev.out_like(), dev.lse_like()
+    c2kv.c2kv_compose_attend_static(plan, dev.pool, dev.q, dev.k_suf, dev.v_suf, out, lse)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and torch.equal(lse, ref_lse)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c2kv.c2kv_compose_attend(plan, dev.pool, dev.q, dev.k_suf, dev.v_suf, out, lse)
+    for _ in range(3):
+        out.zero_()
+        lse.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(lse, ref_lse)
+        run_fused(w, dev=dev, plan=plan)
